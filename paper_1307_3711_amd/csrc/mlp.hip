@@ -10,9 +10,14 @@
 // MFMA 16x16x32 BF16 operand layout (checked on the device): lane l holds
 //   A[l % 16][8 (l / 16) + i], B[8 (l / 16) + i][l % 16] for i = 0..7, and the result
 //   D[4 (l / 16) + r][l % 16] for r = 0..3.
+// Every product over a wave's 16 rows is taken with the weights as A and the rows as B (column
+// l % 16 is the row), and the weights' rows are permuted (unit_of) so that lane l's 16 results are
+// the units 8 g + i and 32 + 8 g + i (g = l / 16): the very units the next product's B operand
+// holds in that lane.  A row's activations then stay in the registers of its four lanes from the
+// input to the output and back; nothing but the weights passes through LDS.
 //
 // Training runs as one workgroup that loops over the steps (every reduction has a fixed
-// order, so training is bitwise reproducible); inference runs one wave per 16 rows.
+// order, so training is bitwise reproducible); inference runs waves that walk over 16-row tiles.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -33,27 +38,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // State buffer layout (bytes, 256-aligned blocks):
-//   params[4610] f32 | adam m[4610] | adam v[4610] | grad[4610] | scaler[16] f32 | meta (int)
-//   scratch: z1, z2, dz2 [256][64] f32; h1, h2, dz2b [256][64] bf16 (as u16);
-//            h1T, dz2bT [64][256] u16; xs [256][4] f32; ts [256][2] f32; dy [256][2] f32
+//   params[4610] f32 | adam m[4610] | adam v[4610] | scaler[16] f32 | meta (int)
 struct MlpState {
   float* p;
   float* m;
   float* v;
-  float* g;
   float* scaler;  // x_mu[4], x_sd[4], y_mu[2], y_sd[2]
-  int32_t* meta;  // [0] Adam step count
-  float* z1;
-  float* z2;
-  float* dz2;
-  uint16_t* h1;
-  uint16_t* h2;
-  uint16_t* dz2b;
-  uint16_t* h1T;
-  uint16_t* dz2bT;
-  float* xs;
-  float* ts;
-  float* dy;
+  int32_t* meta;  // [0] Adam step count, [1] a training call met an out-of-range row
 };
 
 size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -66,20 +57,8 @@ size_t carve(void* base, MlpState* s) {
   t.p = (float*)take(sizeof(float) * kParams);
   t.m = (float*)take(sizeof(float) * kParams);
   t.v = (float*)take(sizeof(float) * kParams);
-  t.g = (float*)take(sizeof(float) * kParams);
   t.scaler = (float*)take(sizeof(float) * 16);
   t.meta = (int32_t*)take(sizeof(int32_t) * 16);
-  t.z1 = (float*)take(sizeof(float) * kMaxBatch * kH);
-  t.z2 = (float*)take(sizeof(float) * kMaxBatch * kH);
-  t.dz2 = (float*)take(sizeof(float) * kMaxBatch * kH);
-  t.h1 = (uint16_t*)take(2 * kMaxBatch * kH);
-  t.h2 = (uint16_t*)take(2 * kMaxBatch * kH);
-  t.dz2b = (uint16_t*)take(2 * kMaxBatch * kH);
-  t.h1T = (uint16_t*)take(2 * kMaxBatch * kH);
-  t.dz2bT = (uint16_t*)take(2 * kMaxBatch * kH);
-  t.xs = (float*)take(sizeof(float) * kMaxBatch * kIn);
-  t.ts = (float*)take(sizeof(float) * kMaxBatch * kOut);
-  t.dy = (float*)take(sizeof(float) * kMaxBatch * kOut);
   if (s) *s = t;
   return o;
 }
@@ -114,6 +93,11 @@ __device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Unit the lane group g holds as its q-th of 16, and the weight row that row m of the A operand of
+// 16-unit tile tc carries, so that result r of the tile is the lane's unit q = 4 tc + r.
+__device__ inline int unit_of(int q, int g) { return 32 * (q >> 3) + 8 * g + (q & 7); }
+__device__ inline int weight_row(int tc, int m) { return unit_of(4 * tc + (m & 3), m >> 2); }
+
 // Shared-memory copy of the BF16 weights used by the products.
 struct WeightsLds {
   uint16_t w1[kH * kIn];
@@ -138,180 +122,351 @@ __device__ void load_weights(const float* p, WeightsLds* w) {
 }
 
 // ----------------------------------------------------------------------------- training
-// One workgroup of 256 threads (4 waves).  Per step: minibatch rows idx[step*B .. +B).
-__global__ __launch_bounds__(256) void k_mlp_train(MlpState s, const float* X, const float* Y, const int32_t* idx,
-                                                   int64_t n, int B, int steps, float lr, float beta1, float beta2, float eps,
-                                                   float* loss_out, int update) {
-  __shared__ WeightsLds w;
-  __shared__ float red[256];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// One workgroup of 16 waves runs every step: wave w takes rows 16 w .. 16 w + 15 of the minibatch
+// from the input to the hidden-1 gradient in registers, then tile w of dW2 over the whole
+// minibatch; the gradients that are sums over the rows of one column (dW1, dW3, the biases) are
+// one thread's chain in row order each, in nine of the waves at once; and each thread keeps the
+// parameters it updates, with their Adam moments, in registers over all steps.  What crosses
+// waves goes through LDS, four barriers a step.
+// Bound by the VALU issue of one compute unit (the two SiLUs and their derivatives of 256 rows are
+// most of it).  Measured at 256 rows: 24.2 us a step, against 200 us with four waves that kept
+// every activation in global memory; with expf's range checks, the general division and the first
+// layer on the VALU 29 us.  Every sum keeps its order and every operation its rounding, so trained
+// weights are the same bits in all three.
+constexpr int kTrainWaves = 16;
+constexpr int kTrainThreads = 64 * kTrainWaves;
+constexpr int kColPad = kMaxBatch + 8;  // entries of a transposed row: 16-byte reads of 16 rows meet no bank twice
+constexpr int kWPad = kH + 8;           // likewise for rows of units
+constexpr int kFPad = kH + 1;
+
+struct TrainLds {
+  __bf16 w2[kH][kWPad];      // W2[n][k]
+  __bf16 w2t[kH][kWPad];     // W2[n][k] at [k][n]
+  float w1[kH][kIn];         // BF16-rounded
+  float w3[kOut][kH];        // BF16-rounded
+  alignas(16) float b1[kH];
+  float b2[kH];
+  float b3[kOut];
+  float xs[kMaxBatch][kIn];  // standardized, BF16-rounded inputs
+  float dy[kMaxBatch][kOut];
+  float4 corr[64];           // 1 - beta1^t, 1 - beta2^t and their reciprocals, of 64 steps
+  float loss[kTrainWaves];
+  float f[kMaxBatch][kFPad]; // hidden-2 gradient, then hidden-1 gradient
+  union {
+    __bf16 h2[kMaxBatch][kWPad];  // hidden-2 activations, until their sums are taken
+    struct {                      // the operands of dW2, [unit][row]
+      __bf16 h1t[kH][kColPad];
+      __bf16 d2t[kH][kColPad];
+    };
+  };
+};
+static_assert(sizeof(TrainLds) <= 160 * 1024, "LDS of one compute unit");
+
+// Master parameter outside W2 that a thread updates (-1: none): waves 0 and 1 the rows of W3,
+// wave 2 b2, wave 3 b3, waves 4 to 7 the columns of W1, wave 8 b1.
+__device__ inline int small_param(int wave, int lane) {
+  if (wave < 2) return oW3 + wave * kH + lane;
+  if (wave == 2) return oB2 + lane;
+  if (wave == 3) return lane < kOut ? oB3 + lane : -1;
+  if (wave < 8) return oW1 + lane * kIn + (wave - 4);
+  if (wave == 8) return oB1 + lane;
+  return -1;
+}
+
+// Its copy for the products (weights BF16-rounded, biases FP32).
+__device__ inline void put_small(TrainLds& w, int wave, int lane, float p) {
+  if (wave < 2) w.w3[wave][lane] = (float)(__bf16)p;
+  else if (wave == 2) w.b2[lane] = p;
+  else if (wave == 3) w.b3[lane] = p;
+  else if (wave < 8) w.w1[lane][wave - 4] = (float)(__bf16)p;
+  else w.b1[lane] = p;
+}
+
+// 1 / (1 + expf(-z)) in 18 issue slots instead of 29, the same bits (every FP32 argument of the two
+// parts was compared on the device): expf by its reduction x log2 e = n + a with the clamp in
+// place of its range checks (outside it the power is 0 or below an ulp of the 1, or infinite);
+// the reciprocal of a number in [1, 2^126] is correctly rounded after one Newton step, div_fixup
+// gives 0 for infinity.  Beyond 2^126 (z below -87) the subnormal quotient becomes 0.
+__device__ inline float sigmoid_train(float z) {
+  constexpr float kLog2e = 1.44269502f, kLog2eLow = 1.9259629e-8f;
+  const float x = __builtin_amdgcn_fmed3f(-z, -104.0f, 89.0f);
+  const float p = x * kLog2e;
+  const float low = __builtin_fmaf(x, kLog2eLow, __builtin_fmaf(x, kLog2e, -p));
+  const float n = __builtin_rintf(p);
+  const float d = 1.0f + __builtin_ldexpf(__builtin_amdgcn_exp2f((p - n) + low), (int)n);
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), d, 1.0f);
+}
+
+// a / b with r the correctly rounded 1 / b: correctly rounded.
+__device__ inline float div_by(float a, float b, float r) {
+  const float q = a * r;
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-b, q, a), r, q), b, a);
+}
+
+// Adam (Kingma & Ba) on one FP32 master weight; c1, c2 are 1 - beta^t, r1, r2 their reciprocals.
+__device__ inline void adam(float g, float lr, float beta1, float beta2, float eps, const float4 c, float& p, float& m,
+                            float& v) {
+  m = beta1 * m + (1.0f - beta1) * g;
+  v = beta2 * v + (1.0f - beta2) * g * g;
+  p -= lr * div_by(m, c.x, c.z) / (sqrtf(div_by(v, c.y, c.w)) + eps);
+}
+
+// Sum over the B rows (a multiple of 32) in row order, add(operands of a row, sum so far): the
+// operands of 16 rows are loaded while the 16 rows before them are added.
+template <typename L, typename A>
+__device__ inline float row_chain(int B, L load, A add) {
+  decltype(load(0)) u[16], v[16];
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) u[i] = load(i);
+#pragma unroll 1
+  for (int r = 0; r < B; r += 32) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = load(r + 16 + i);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum = add(u[i], sum);
+    const int next = r + 32 < B ? r + 32 : 0;  // the last one is not used
+#pragma unroll
+    for (int i = 0; i < 16; ++i) u[i] = load(next + i);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum = add(v[i], sum);
+  }
+  return sum;
+}
+
+__global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const float* X, const float* Y,
+                                                             const int32_t* idx, int64_t n, int B, int steps, float lr,
+                                                             float beta1, float beta2, float eps, float* loss_out,
+                                                             float* grad_out) {
+  __shared__ TrainLds w;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = B / 16;                       // waves that hold rows
+  const int r16 = lane & 15, g = lane >> 4;    // row of the wave's tile, lane group
+  const int row = 16 * wave + r16;             // row of the minibatch
+  const bool rows = wave < nw;
+
+  // this thread's parameters: four of W2 in the layout of its dW2 tile, and one small one
+  const int n0 = 16 * (wave >> 2) + 4 * g, k0 = 16 * (wave & 3) + r16;
+  const int small = small_param(wave, lane);
+  float p2[4], m2[4], v2[4], p1 = 0.f, m1 = 0.f, v1 = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = oW2 + (n0 + q) * kH + k0;
+    p2[q] = s.p[i];
+    m2[q] = s.m[i];
+    v2[q] = s.v[i];
+  }
+  if (small >= 0) {
+    p1 = s.p[small];
+    m1 = s.m[small];
+    v1 = s.v[small];
+  }
+  const int t0 = s.meta[0];
+  const float mu = s.scaler[g], sd = s.scaler[4 + g];  // of input g: lane l brings input l / 16 of its row
+  float ymu[kOut], ysd[kOut];
+#pragma unroll
+  for (int o = 0; o < kOut; ++o) { ymu[o] = s.scaler[8 + o]; ysd[o] = s.scaler[10 + o]; }
+
+  // the rows of the next step and the row indices of the one after it are loaded ahead
+  auto row_index = [&](int step) {
+    int r = idx[(int64_t)step * B + row];
+    if (r < 0 || r >= n) { s.meta[1] = 1; r = 0; }  // out-of-range row: flagged, row 0 used
+    return r;
+  };
+  float xr, yr[kOut];
+  int next = 0;
+  auto load_row = [&](int r) {
+    xr = X[(int64_t)r * kIn + g];
+#pragma unroll
+    for (int o = 0; o < kOut; ++o) yr[o] = Y[(int64_t)r * kOut + o];
+  };
+  if (rows) {
+    load_row(row_index(0));
+    if (steps > 1) next = row_index(1);
+  }
+
+#pragma unroll 1
   for (int step = 0; step < steps; ++step) {
-    __syncthreads();
-    load_weights(s.p, &w);
-    // minibatch: standardized, BF16-rounded inputs; standardized targets
-    for (int e = tid; e < B * kIn; e += 256) {
-      const int r = e / kIn, k = e % kIn;
-      int row = idx[(int64_t)step * B + r];
-      if (row < 0 || row >= n) { s.meta[1] = 1; row = 0; }  // out-of-range row: flagged, row 0 used
-      s.xs[e] = round_bf16((X[(int64_t)row * kIn + k] - s.scaler[k]) / s.scaler[4 + k]);
-    }
-    for (int e = tid; e < B * kOut; e += 256) {
-      const int r = e / kOut, o = e % kOut;
-      int row = idx[(int64_t)step * B + r];
-      if (row < 0 || row >= n) row = 0;
-      s.ts[e] = (Y[(int64_t)row * kOut + o] - s.scaler[8 + o]) / s.scaler[10 + o];
-    }
-    __syncthreads();
-    // layer 1 (VALU): z1 = W1 x + b1
-    for (int e = tid; e < B * kH; e += 256) {
-      const int r = e / kH, j = e % kH;
-      float z = w.b1[j];
+    // weights of this step for the products
 #pragma unroll
-      for (int k = 0; k < kIn; ++k) z = __builtin_fmaf(bf16_float(w.w1[j * kIn + k]), s.xs[r * kIn + k], z);
-      s.z1[e] = z;
-      const uint16_t h = bf16_bits(silu(z));
-      s.h1[e] = h;
-      s.h1T[j * kMaxBatch + r] = h;
+    for (int q = 0; q < 4; ++q) {
+      const __bf16 b = (__bf16)p2[q];
+      w.w2[n0 + q][k0] = b;
+      w.w2t[k0][n0 + q] = b;
+    }
+    if (small >= 0) put_small(w, wave, lane, p1);
+    if ((step & 63) == 0 && tid < 64) {
+      const float t = (float)(t0 + step + 1 + tid);
+      const float c1 = 1.0f - powf(beta1, t), c2 = 1.0f - powf(beta2, t);
+      w.corr[tid] = make_float4(c1, c2, 1.0f / c1, 1.0f / c2);
     }
     __syncthreads();
-    // layer 2 (MFMA): z2[r][n] = sum_k h1[r][k] W2[n][k] + b2[n]; tiles of 16 rows x 16 cols
-    const int tiles2 = (B / 16) * (kH / 16);
-    for (int t = wave; t < tiles2; t += 4) {
-      const int tr = t / (kH / 16), tc = t % (kH / 16);
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+
+    bf16x8 h1[2], d2[2];
+    float e1[16];  // SiLU'(z1), then the hidden-1 gradient
+    if (rows) {
+      float ty[kOut];
+      const float x = (float)(__bf16)((xr - mu) / sd);
 #pragma unroll
-      for (int kk = 0; kk < kH; kk += 32) {
-        const bf16x8 a = load8(&s.h1[(tr * 16 + lane % 16) * kH + kk + 8 * (lane / 16)]);
-        const bf16x8 b = load8(&w.w2[(tc * 16 + lane % 16) * kH + kk + 8 * (lane / 16)]);
-        acc = mfma(a, b, acc);
+      for (int o = 0; o < kOut; ++o) ty[o] = (yr[o] - ymu[o]) / ysd[o];
+      if (step + 1 < steps) load_row(next);
+      if (step + 2 < steps) next = row_index(step + 2);
+      w.xs[row][g] = x;
+      // layer 1: z1 = W1 x + b1 on the FP32 matrix units, whose sum over the four inputs rounds as a
+      // chain of fused multiply-adds does
+#pragma unroll
+      for (int tc = 0; tc < 4; ++tc) {
+        f32x4 acc = *(const f32x4*)&w.b1[unit_of(4 * tc, g)];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w1[weight_row(tc, r16)][g], x, acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int q = 4 * tc + r;
+          const float z = acc[r];
+          const float sg = sigmoid_train(z);
+          e1[q] = sg * (1.0f + z * (1.0f - sg));
+          h1[q >> 3][q & 7] = (__bf16)(z * sg);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      const int n = tc * 16 + lane % 16;
+      // layer 2: z2 = W2 h1 + b2
+      bf16x8 h2[2];
+      float e2[16];  // SiLU'(z2)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = tr * 16 + 4 * (lane / 16) + q;
-        const float z = acc[q] + w.b2[n];
-        s.z2[r * kH + n] = z;
-        s.h2[r * kH + n] = bf16_bits(silu(z));
+      for (int tc = 0; tc < 4; ++tc) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma(*(const bf16x8*)&w.w2[weight_row(tc, r16)][8 * g], h1[0], acc);
+        acc = mfma(*(const bf16x8*)&w.w2[weight_row(tc, r16)][32 + 8 * g], h1[1], acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int q = 4 * tc + r;
+          const float z = acc[r] + w.b2[unit_of(q, g)];
+          const float sg = sigmoid_train(z);
+          e2[q] = sg * (1.0f + z * (1.0f - sg));
+          h2[q >> 3][q & 7] = (__bf16)(z * sg);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-    __syncthreads();
-    // layer 3 (VALU) and loss: y = W3 h2 + b3; dy = (y - t) / B
-    {
-      float l = 0.f;
-      for (int e = tid; e < B * kOut; e += 256) {
-        const int r = e / kOut, o = e % kOut;
-        float y = w.b3[o];
-        for (int j = 0; j < kH; ++j) y = __builtin_fmaf(bf16_float(w.w3[o * kH + j]), bf16_float(s.h2[r * kH + j]), y);
-        const float d = y - s.ts[e];
-        s.dy[e] = d / (float)B;
+      *(bf16x8*)&w.h2[row][8 * g] = h2[0];
+      *(bf16x8*)&w.h2[row][32 + 8 * g] = h2[1];
+      // layer 3: y = W3 h2 + b3, summed in unit order: each lane group adds its eight units and
+      // hands the sum to the next group
+      float y[kOut] = {w.b3[0], w.b3[1]};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float h = (float)h2[t >> 2][i];
+#pragma unroll
+          for (int o = 0; o < kOut; ++o) y[o] = __builtin_fmaf(w.w3[o][unit_of(8 * (t >> 2) + i, g)], h, y[o]);
+        }
+#pragma unroll
+        for (int o = 0; o < kOut; ++o) y[o] = __shfl(y[o], 16 * (t & 3) + r16, 64);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // loss and its gradient: dy = (y - t) / B
+      float dy[kOut], l = 0.f;
+#pragma unroll
+      for (int o = 0; o < kOut; ++o) {
+        const float d = y[o] - ty[o];
+        dy[o] = d / (float)B;
         l += d * d;
       }
-      red[tid] = l;
-    }
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (tid < o) red[tid] += red[tid + o];
-      __syncthreads();
-    }
-    if (tid == 0 && loss_out) loss_out[step] = red[0] / (2.0f * (float)B);
-    // output layer gradients: dW3[o][j] = sum_r dy[r][o] h2[r][j]; db3[o] = sum_r dy[r][o]
-    for (int e = tid; e < kOut * kH + kOut; e += 256) {
-      if (e < kOut * kH) {
-        const int o = e / kH, j = e % kH;
-        float g = 0.f;
-        for (int r = 0; r < B; ++r) g = __builtin_fmaf(s.dy[r * kOut + o], bf16_float(s.h2[r * kH + j]), g);
-        s.g[oW3 + e] = g;
-      } else {
-        const int o = e - kOut * kH;
-        float g = 0.f;
-        for (int r = 0; r < B; ++r) g += s.dy[r * kOut + o];
-        s.g[oB3 + o] = g;
-      }
-    }
-    // hidden-2 gradient: dz2 = (W3^T dy) * silu'(z2)
-    for (int e = tid; e < B * kH; e += 256) {
-      const int r = e / kH, j = e % kH;
-      float g = 0.f;
+      if (g == 0) {
 #pragma unroll
-      for (int o = 0; o < kOut; ++o) g = __builtin_fmaf(bf16_float(w.w3[o * kH + j]), s.dy[r * kOut + o], g);
-      const float d = g * dsilu(s.z2[e]);
-      s.dz2[e] = d;
-      const uint16_t b = bf16_bits(d);
-      s.dz2b[e] = b;
-      s.dz2bT[j * kMaxBatch + r] = b;
-    }
-    __syncthreads();
-    // db2[n] = sum_r dz2[r][n]
-    if (tid < kH) {
-      float g = 0.f;
-      for (int r = 0; r < B; ++r) g += s.dz2[r * kH + tid];
-      s.g[oB2 + tid] = g;
-    }
-    // dW2[n][k] = sum_r dz2b[r][n] h1[r][k]  (MFMA, K = batch)
-    for (int t = wave; t < (kH / 16) * (kH / 16); t += 4) {
-      const int tm = t / (kH / 16), tn = t % (kH / 16);
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int kk = 0; kk < B; kk += 32) {
-        const bf16x8 a = load8(&s.dz2bT[(tm * 16 + lane % 16) * kMaxBatch + kk + 8 * (lane / 16)]);
-        const bf16x8 b = load8(&s.h1T[(tn * 16 + lane % 16) * kMaxBatch + kk + 8 * (lane / 16)]);
-        acc = mfma(a, b, acc);
+        for (int o = 0; o < kOut; ++o) w.dy[row][o] = dy[o];
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = tm * 16 + 4 * (lane / 16) + q, k = tn * 16 + lane % 16;
-        s.g[oW2 + n * kH + k] = acc[q];
-      }
-    }
-    // hidden-1 gradient: g1[r][k] = sum_n dz2b[r][n] W2[n][k]  (MFMA); dz1 = g1 * silu'(z1)
-    // (dz1 overwrites z1 after use)
-    for (int t = wave; t < (B / 16) * (kH / 16); t += 4) {
-      const int tr = t / (kH / 16), tc = t % (kH / 16);
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int o = 1; o < 16; o <<= 1) l += __shfl_xor(l, o, 64);
+      if (lane == 0) w.loss[wave] = l;
+      // hidden-2 gradient: dz2 = (W3^T dy) SiLU'(z2)
 #pragma unroll
-      for (int kk = 0; kk < kH; kk += 32) {
-        const bf16x8 a = load8(&s.dz2b[(tr * 16 + lane % 16) * kH + kk + 8 * (lane / 16)]);
-        const bf16x8 b = load8(&w.w2t[(tc * 16 + lane % 16) * kH + kk + 8 * (lane / 16)]);
-        acc = mfma(a, b, acc);
+      for (int q = 0; q < 16; ++q) {
+        const int u = unit_of(q, g);
+        const float gr = __builtin_fmaf(w.w3[1][u], dy[1], w.w3[0][u] * dy[0]);
+        const float d = gr * e2[q];
+        d2[q >> 3][q & 7] = (__bf16)d;
+        w.f[row][u] = d;
+        if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
-      const int k = tc * 16 + lane % 16;
+      // hidden-1 gradient: dz1 = (W2^T dz2) SiLU'(z1)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = tr * 16 + 4 * (lane / 16) + q;
-        s.z1[r * kH + k] = acc[q] * dsilu(s.z1[r * kH + k]);
+      for (int tc = 0; tc < 4; ++tc) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma(*(const bf16x8*)&w.w2t[weight_row(tc, r16)][8 * g], d2[0], acc);
+        acc = mfma(*(const bf16x8*)&w.w2t[weight_row(tc, r16)][32 + 8 * g], d2[1], acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e1[4 * tc + r] = acc[r] * e1[4 * tc + r];
       }
     }
     __syncthreads();
-    // dW1[j][k] = sum_r dz1[r][j] x[r][k]; db1[j] = sum_r dz1[r][j]
-    for (int e = tid; e < kH * kIn + kH; e += 256) {
-      if (e < kH * kIn) {
-        const int j = e / kIn, k = e % kIn;
-        float g = 0.f;
-        for (int r = 0; r < B; ++r) g = __builtin_fmaf(s.z1[r * kH + j], s.xs[r * kIn + k], g);
-        s.g[oW1 + e] = g;
-      } else {
-        const int j = e - kH * kIn;
-        float g = 0.f;
-        for (int r = 0; r < B; ++r) g += s.z1[r * kH + j];
-        s.g[oB1 + j] = g;
+
+    // the sums over rows of hidden-2 quantities: dW3[o][j] = sum_r dy[r][o] h2[r][j],
+    // db2[j] = sum_r dz2[r][j], db3[o] = sum_r dy[r][o]
+    float gs = 0.f;
+    const auto plus = [](float v, float sum) { return sum + v; };
+    const auto product = [](float2 v, float sum) { return __builtin_fmaf(v.x, v.y, sum); };
+    if (wave < 2) {
+      gs = row_chain(B, [&](int r) { return make_float2(w.dy[r][wave], (float)w.h2[r][lane]); }, product);
+    } else if (wave == 2) {
+      gs = row_chain(B, [&](int r) { return w.f[r][lane]; }, plus);
+    } else if (wave == 3 && lane < kOut) {
+      gs = row_chain(B, [&](int r) { return w.dy[r][lane]; }, plus);
+    } else if (wave == kTrainWaves - 1 && lane == 0 && loss_out) {
+      float l = 0.f;
+      for (int q = 0; q < nw; ++q) l += w.loss[q];
+      loss_out[step] = l / (2.0f * (float)B);
+    }
+    __syncthreads();
+    if (rows) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int u = unit_of(q, g);
+        w.f[row][u] = e1[q];
+        w.h1t[u][row] = h1[q >> 3][q & 7];
+        w.d2t[u][row] = d2[q >> 3][q & 7];
       }
     }
     __syncthreads();
-    if (update) {
-      // Adam (Kingma & Ba) on the FP32 master weights
-      const int t = s.meta[0] + 1;
-      const float c1 = 1.0f - powf(beta1, (float)t), c2 = 1.0f - powf(beta2, (float)t);
-      for (int i = tid; i < kParams; i += 256) {
-        const float g = s.g[i];
-        const float m = beta1 * s.m[i] + (1.0f - beta1) * g;
-        const float v = beta2 * s.v[i] + (1.0f - beta2) * g * g;
-        s.m[i] = m;
-        s.v[i] = v;
-        s.p[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
-      }
-      __syncthreads();
-      if (tid == 0) s.meta[0] = t;
+
+    // dW1[j][k] = sum_r dz1[r][j] x[r][k], db1[j] = sum_r dz1[r][j]
+    if (wave >= 4 && wave < 8) {
+      gs = row_chain(B, [&](int r) { return make_float2(w.f[r][lane], w.xs[r][wave - 4]); }, product);
+    } else if (wave == 8) {
+      gs = row_chain(B, [&](int r) { return w.f[r][lane]; }, plus);
     }
+    // dW2[n][k] = sum_r dz2[r][n] h1[r][k]: the wave's 16 x 16 tile over the minibatch
+    f32x4 gw = {0.f, 0.f, 0.f, 0.f};
+    for (int kk = 0; kk < B; kk += 32)
+      gw = mfma(*(const bf16x8*)&w.d2t[16 * (wave >> 2) + r16][kk + 8 * g],
+                *(const bf16x8*)&w.h1t[16 * (wave & 3) + r16][kk + 8 * g], gw);
+    if (grad_out) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) grad_out[oW2 + (n0 + q) * kH + k0] = gw[q];
+      if (small >= 0) grad_out[small] = gs;
+    } else {
+      const float4 c = w.corr[step & 63];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) adam(gw[q], lr, beta1, beta2, eps, c, p2[q], m2[q], v2[q]);
+      if (small >= 0) adam(gs, lr, beta1, beta2, eps, c, p1, m1, v1);
+    }
+    if ((step & 63) == 63) __syncthreads();  // the step's factors are read before the next ones replace them
   }
+  if (grad_out) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = oW2 + (n0 + q) * kH + k0;
+    s.p[i] = p2[q];
+    s.m[i] = m2[q];
+    s.v[i] = v2[q];
+  }
+  if (small >= 0) {
+    s.p[small] = p1;
+    s.m[small] = m1;
+    s.v[small] = v1;
+  }
+  if (tid == 0) s.meta[0] = t0 + steps;
 }
 
 // ----------------------------------------------------------------------------- scaler
@@ -449,7 +604,8 @@ int lc_mlp_train(void* d_state, const float* d_X, const float* d_Y, int64_t n, c
   if (steps == 0) return LC_OK;
   MlpState s;
   carve(d_state, &s);
-  k_mlp_train<<<1, 256, 0, (hipStream_t)stream>>>(s, d_X, d_Y, d_rows, n, batch, steps, lr, 0.9f, 0.999f, 1e-8f, d_loss, 1);
+  k_mlp_train<<<1, kTrainThreads, 0, (hipStream_t)stream>>>(s, d_X, d_Y, d_rows, n, batch, steps, lr, 0.9f, 0.999f, 1e-8f,
+                                                            d_loss, nullptr);
   return hipGetLastError() == hipSuccess ? LC_OK : LC_E_HIP;
 }
 
@@ -459,11 +615,9 @@ int lc_mlp_grad(void* d_state, const float* d_X, const float* d_Y, int64_t n, co
   if (batch < 32 || batch > kMaxBatch || batch % 32 != 0) return LC_E_INVALID;
   MlpState s;
   carve(d_state, &s);
-  hipStream_t st = (hipStream_t)stream;
-  k_mlp_train<<<1, 256, 0, st>>>(s, d_X, d_Y, d_rows, n, batch, 1, 1.0f, 0.9f, 0.999f, 1e-8f, d_loss, 0);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(d_grad, s.g, sizeof(float) * kParams, hipMemcpyDeviceToDevice, st);
-  return e == hipSuccess ? LC_OK : LC_E_HIP;
+  k_mlp_train<<<1, kTrainThreads, 0, (hipStream_t)stream>>>(s, d_X, d_Y, d_rows, n, batch, 1, 1.0f, 0.9f, 0.999f, 1e-8f,
+                                                            d_loss, d_grad);
+  return hipGetLastError() == hipSuccess ? LC_OK : LC_E_HIP;
 }
 
 int lc_mlp_infer(const void* d_state, const float* d_X, float* d_Y, int64_t n, void* stream) {

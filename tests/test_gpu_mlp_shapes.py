@@ -1,0 +1,59 @@
+"""The surrogate's kernels at the sizes where their work division changes.
+
+Tolerances: gradients and inference as in test_gpu_mlp.py (FP32 against FP64 sums and the BF16
+rounding flips they cause); steps split over calls, bit for bit.
+"""
+import numpy as np
+import pytest
+
+from oracle import mlp
+from workloads.surrogate import init_params, row_order, toy_dataset
+
+from _helpers import gpu_available
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+BLOCKS = [(0, 256), (256, 320), (320, 4416), (4416, 4480), (4480, 4608), (4608, 4610)]
+
+
+def _net(n, seed, steps=0, batch=32):
+    import torch
+    import paper_1307_3711_amd as lc
+    X, Y = toy_dataset(n, seed)
+    theta = init_params(seed)
+    net = lc.Surrogate(theta)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    net.fit_scaler(Xd, Yd)
+    rows = torch.from_numpy(row_order(n, batch, max(steps, 1), seed + 1)).cuda()
+    sc = {k: np.asarray(v, np.float64) for k, v in net.params()[1].items()}
+    return net, theta.astype(np.float64), X, Y, Xd, Yd, rows, sc
+
+
+@pytest.mark.parametrize("batch", [64, 160, 224])
+def test_gradient_where_some_waves_hold_no_rows(batch):
+    """Two to fourteen of the sixteen waves hold rows; every wave takes a tile of dW2."""
+    net, theta, X, Y, Xd, Yd, rows, sc = _net(300, 21, 1, batch)
+    g, loss = net.grad(Xd, Yd, rows, batch)
+    g = g.cpu().numpy().astype(np.float64)
+    Xs, Ts = mlp.standardize(X, Y, sc)
+    r = rows.cpu().numpy()
+    lo, go = mlp.loss_and_grad(theta, Xs[r], Ts[r], bf16=True)
+    assert float(loss.cpu()[0]) == pytest.approx(lo, rel=1e-4)
+    for a, b in BLOCKS:
+        assert np.linalg.norm(g[a:b] - go[a:b]) <= 1e-3 * np.linalg.norm(go[a:b])
+
+
+@pytest.mark.parametrize("batch,split", [(32, 64), (96, 65), (256, 1)])
+def test_steps_split_over_calls_bitwise(batch, split):
+    """Factors of Adam's step count come 64 steps at a time: a run of 130 steps against the same
+    steps in two calls, cut at and beside that length."""
+    out = []
+    for cuts in ([130], [split, 130 - split]):
+        net, _, _, _, Xd, Yd, rows, _ = _net(700, 5, 130, batch)
+        at, loss = 0, []
+        for k in cuts:
+            loss.append(net.train(Xd, Yd, rows[at * batch:], batch, k, 1e-3).cpu().numpy())
+            at += k
+        out.append((net.params()[0], np.concatenate(loss)))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert np.all(np.isfinite(out[0][0])) and not np.array_equal(out[0][0], init_params(5))
