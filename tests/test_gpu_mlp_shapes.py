@@ -57,3 +57,29 @@ def test_steps_split_over_calls_bitwise(batch, split):
         out.append((net.params()[0], np.concatenate(loss)))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert np.all(np.isfinite(out[0][0])) and not np.array_equal(out[0][0], init_params(5))
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 65, 4096, 65536, 65537, 131111])
+def test_inference_at_tile_edges(n):
+    """16 rows a tile, 64 a block; from 65,536 rows on a wave takes more than one tile."""
+    import torch
+    net, theta, _, _, _, _, _, sc = _net(512, 31)
+    X, _ = toy_dataset(n, 77)
+    out = net.infer(torch.from_numpy(X).cuda())
+    assert out.shape == (n, 2)
+    d = np.abs(out.cpu().numpy().astype(np.float64) - mlp.infer(theta, X, sc, bf16=True)) / sc["y_sd"]
+    assert d.max() <= 2e-2 and np.quantile(d, 0.99) <= 1e-4
+
+
+def test_inference_keeps_nonfinite_rows_apart():
+    """A row with an infinity or NaN gives no finite answer and leaves its tile's other rows alone."""
+    import torch
+    net, theta, _, _, _, _, _, sc = _net(512, 31)
+    X, _ = toy_dataset(40, 78)
+    ref = net.infer(torch.from_numpy(X).cuda()).cpu().numpy()
+    for row, value in ((3, np.nan), (17, np.inf), (33, -np.inf)):
+        bad = X.copy()
+        bad[row, 1] = value
+        out = net.infer(torch.from_numpy(bad).cuda()).cpu().numpy()
+        keep = np.arange(40) != row
+        assert np.array_equal(out[keep], ref[keep]) and not np.isfinite(out[row]).any()
