@@ -400,7 +400,7 @@ int lc_mlp_set_params(void* d_state, const float* host_params, void* hip_stream)
 int lc_mlp_get_params(const void* d_state, float* host_params, float* host_scaler, void* hip_stream);
 
 /* Population mean and standard deviation of every input and target column over n rows
- * (FP64 sums in row order), stored as the scaler.  Asynchronous. */
+ * (FP64 sums in a fixed order), stored as the scaler.  Asynchronous. */
 int lc_mlp_fit_scaler(void* d_state, const float* d_X, const float* d_Y, int64_t n, void* hip_stream);
 
 /* steps Adam steps (lr, beta1 0.9, beta2 0.999, eps 1e-8) on minibatches of `batch` rows

@@ -423,25 +423,56 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
 }
 
 // ----------------------------------------------------------------------------- scaler
-// Feature and target means and standard deviations (population), FP64 sums in row order.
-__global__ __launch_bounds__(64) void k_mlp_scaler(MlpState s, const float* X, const float* Y, int64_t n) {
-  const int c = threadIdx.x;  // column: 0..3 features, 4..5 targets
-  if (c >= kIn + kOut) return;
-  const float* src = c < kIn ? X : Y;
-  const int stride = c < kIn ? kIn : kOut;
-  const int col = c < kIn ? c : c - kIn;
+// Feature and target means and standard deviations (population) in two passes of FP64 sums, one
+// workgroup.  A thread walks the flat arrays with a stride that is a multiple of the row length,
+// so it meets one column only and the loads are coalesced; the threads of a column then add up
+// over the lanes and the waves in a fixed order.  Latency-bound: one thread per column in row order
+// took 589 us for 3686 rows, this 8.8 us (loads of eight elements in flight per thread).
+constexpr int kScalerThreads = 1024;
+static_assert(kScalerThreads % kIn == 0 && kScalerThreads % kOut == 0, "a thread meets one column");
+
+// Sum over the elements of the thread's column of f(element), for every column of a row of W.
+// Returns the column's total to each of its threads.
+template <int W, typename F>
+__device__ inline double column_sum(const float* src, int64_t elems, double (*sh)[kIn], F f) {
+  constexpr int kAhead = 8;  // loads in flight
+  const int tid = threadIdx.x;
   double sum = 0.0;
-  for (int64_t i = 0; i < n; ++i) sum += (double)src[i * stride + col];
-  const double mu = sum / (double)n;
-  double ss = 0.0;
-  for (int64_t i = 0; i < n; ++i) {
-    const double d = (double)src[i * stride + col] - mu;
-    ss += d * d;
+  int64_t e = tid;
+  for (; e + (kAhead - 1) * kScalerThreads < elems; e += kAhead * kScalerThreads) {
+    float v[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) v[i] = src[e + i * kScalerThreads];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) sum += f((double)v[i]);
   }
+  for (; e < elems; e += kScalerThreads) sum += f((double)src[e]);
+  for (int o = 32; o >= W; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  __syncthreads();  // the previous sum's readers are done
+  if ((tid & 63) < W) sh[tid >> 6][tid & 63] = sum;
+  __syncthreads();
+  double total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kScalerThreads / 64; ++w) total += sh[w][tid % W];
+  return total;
+}
+
+template <int W>
+__device__ inline void fit_columns(const float* src, int64_t n, double (*sh)[kIn], float* mean, float* dev) {
+  const double mu = column_sum<W>(src, n * W, sh, [](double x) { return x; }) / (double)n;
+  const double ss = column_sum<W>(src, n * W, sh, [mu](double x) { return (x - mu) * (x - mu); });
   double sd = sqrt(ss / (double)n);
   if (!(sd > 0.0)) sd = 1.0;
-  if (c < kIn) { s.scaler[col] = (float)mu; s.scaler[4 + col] = (float)sd; }
-  else { s.scaler[8 + col] = (float)mu; s.scaler[10 + col] = (float)sd; }
+  if (threadIdx.x < W) {
+    mean[threadIdx.x] = (float)mu;
+    dev[threadIdx.x] = (float)sd;
+  }
+}
+
+__global__ __launch_bounds__(kScalerThreads) void k_mlp_scaler(MlpState s, const float* X, const float* Y, int64_t n) {
+  __shared__ double sh[kScalerThreads / 64][kIn];
+  fit_columns<kIn>(X, n, sh, s.scaler, s.scaler + 4);
+  fit_columns<kOut>(Y, n, sh, s.scaler + 8, s.scaler + 10);
 }
 
 // ----------------------------------------------------------------------------- inference
@@ -579,7 +610,7 @@ int lc_mlp_fit_scaler(void* d_state, const float* d_X, const float* d_Y, int64_t
   if (!d_state || !d_X || !d_Y || n < 1 || ((uintptr_t)d_state & 255)) return LC_E_INVALID;
   MlpState s;
   carve(d_state, &s);
-  k_mlp_scaler<<<1, 64, 0, (hipStream_t)stream>>>(s, d_X, d_Y, n);
+  k_mlp_scaler<<<1, kScalerThreads, 0, (hipStream_t)stream>>>(s, d_X, d_Y, n);
   return hipGetLastError() == hipSuccess ? LC_OK : LC_E_HIP;
 }
 

@@ -83,3 +83,21 @@ def test_inference_keeps_nonfinite_rows_apart():
         out = net.infer(torch.from_numpy(bad).cuda()).cpu().numpy()
         keep = np.arange(40) != row
         assert np.array_equal(out[keep], ref[keep]) and not np.isfinite(out[row]).any()
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 257, 1023, 2049, 4096, 16387])
+def test_scaler_sizes_and_constant_column(n):
+    """Fewer elements than threads, whole and ragged rounds of loads; a constant column has
+    deviation 1.  FP64 sums of FP32 values: the FP32 result is within an ulp of numpy's."""
+    import torch
+    import paper_1307_3711_amd as lc
+    X, Y = toy_dataset(n, 91)
+    X[:, 2] = 3.25
+    net = lc.Surrogate(init_params(1))
+    net.fit_scaler(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda())
+    _, sc = net.params()
+    for a, mu, sd in ((X, sc["x_mu"], sc["x_sd"]), (Y, sc["y_mu"], sc["y_sd"])):
+        a = a.astype(np.float64)
+        want = a.std(axis=0)
+        assert np.allclose(mu, a.mean(axis=0), rtol=1.2e-7, atol=1e-30)
+        assert np.allclose(sd, np.where(want > 0, want, 1.0), rtol=1.2e-7, atol=0)
