@@ -1319,6 +1319,16 @@ extern "C" int lc_profile_steps(lc_sim* s, int64_t n_steps, double* out_ms, int6
 }
 
 // ----------------------------------------------------------------------------- standalone field
+namespace {
+
+// No tiling asked for: field.hip chooses by size.
+bool field_default(const lc_tuning* t) {
+  return !t || !(t->targets_per_lane || t->waves_per_target || t->tile_sources || t->j_splits || t->persistent ||
+                 t->scalar_sources || t->newton3);
+}
+
+}  // namespace
+
 size_t lc_field_workspace_bytes(int32_t precision, int64_t n, const lc_tuning* t) {
   if (precision < LC_FP64 || precision > LC_FP32_KAHAN || n < 0) return 0;
   ForceTiling ft = default_tiling(precision);
@@ -1332,7 +1342,8 @@ size_t lc_field_workspace_bytes(int32_t precision, int64_t n, const lc_tuning* t
     ft.newton3 = t->newton3 ? 1 : 0;
   }
   if (!force_tiling_valid(precision, ft)) return 0;
-  return field_workspace_bytes(precision, n, ft);
+  const size_t b = field_workspace_bytes(precision, n, ft);
+  return field_default(t) ? std::max(b, field_default_bytes(precision, n)) : b;
 }
 
 namespace {
@@ -1372,7 +1383,9 @@ int lc_field(int32_t precision, int64_t n, const double* d_xyzq, double eps2, do
   if (n > 0 && !d_work) return LC_E_INVALID;
   if (((uintptr_t)d_work & 255) != 0) return LC_E_INVALID;
   if (work_bytes < field_workspace_bytes(precision, n, ft)) return LC_E_INVALID;
-  hipError_t e = launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, ft, (hipStream_t)hip_stream);
+  hipError_t e = field_default(t)
+                     ? launch_field_default(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, work_bytes, (hipStream_t)hip_stream)
+                     : launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, ft, (hipStream_t)hip_stream);
   return e == hipSuccess ? LC_OK : LC_E_HIP;
 }
 
@@ -1385,7 +1398,9 @@ int lc_field_static(int32_t precision, int64_t n, const double* d_xyzq, double e
   void* work = nullptr;
   hipError_t e = field_scratch(&work);
   if (e == hipSuccess)
-    e = launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, work, ft, (hipStream_t)hip_stream);
+    e = field_default(t) ? launch_field_default(precision, n, d_xyzq, eps2, d_E, d_phi, work, LC_FIELD_STATIC_MAX_BYTES,
+                                                (hipStream_t)hip_stream)
+                         : launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, work, ft, (hipStream_t)hip_stream);
   return e == hipSuccess ? LC_OK : LC_E_HIP;
 }
 

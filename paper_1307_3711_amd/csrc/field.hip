@@ -1,0 +1,418 @@
+// field.hip -- the softened Coulomb field of charges on themselves with the default tiling
+// (lc_field, lc_field_static), Sec. II:
+//
+//   E_i   = sum_{j != i} q_j (r_i - r_j) / (|r_i - r_j|^2 + eps^2)^{3/2}
+//   phi_i = sum_{j != i} q_j / (|r_i - r_j|^2 + eps^2)^{1/2}        (when asked for)
+#include <algorithm>
+
+#include "lc_internal.h"
+#include "pair_math.h"
+
+namespace lc {
+namespace {
+
+// One launch, straight from the caller's arrays to the caller's results.  A block takes 16 R
+// targets and all sources, which it stages kChunk at a time in LDS in the pair type; the 64 lanes
+// of a wave are 16 target columns (R targets each) x 4 sources, so the block's 16 waves meet 64
+// sources at a time and a small n still fills the chip.  The 64 partial sums of a target are added
+// in a fixed order; sums run in the pair type over a lane's sources of one chunk (32), in FP64
+// beyond.
+// Bound by launch and load latency below a few thousand charges, by VALU issue beyond.  Measured a
+// call (field and potential): 1000 charges in FP64 13 us, 4099 with Kahan sums 28 us, against 120
+// and 902 us with the one-sided tiling of force.hip that a default call took before (blocks of 512
+// or 1024 targets: 2 and 5 of them on 256 compute units).  Two and four targets per lane were
+// slower at every size from 4000 charges on (20,000 FP32: 222 and 243 us against 174 us): one
+// block of 16 waves per compute unit instead of two waits at every chunk's barriers.
+constexpr int kCols = 16;              // target columns of a block
+constexpr int kGroups = 64 / kCols;    // sources a wave meets at a time
+constexpr int kWaves = 16;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kStep = kGroups * kWaves;  // sources the block meets at a time
+constexpr int kChunk = 2048;
+constexpr int64_t kGrid = 1 << 20;  // blocks of a launch at most (they stride over the targets)
+
+// The lane's targets and their sums over a chunk (c: Kahan compensations).
+template <typename T, int R>
+struct Lane {
+  T x[R], y[R], z[R];
+  T f[R][4], c[R][4];
+};
+
+template <typename T, bool KAHAN>
+__device__ inline void add_term(T a, T b, T& f, T& c) {  // f += a b
+  if (KAHAN) {
+    const T y = n3_fma(a, b, -c), t = f + y;
+    c = (t - f) - y;
+    f = t;
+  } else {
+    f = n3_fma(a, b, f);
+  }
+}
+
+// One source against the lane's targets.  UNIFORM: the charge is left to the caller.  MASK: the
+// source counts only if live, and not in the potential of target r when self == 16 r.
+template <typename T, int R, bool KAHAN, bool PHI, bool UNIFORM, bool MASK, typename V4>
+__device__ inline void direct_pair(const V4 s, bool live, int64_t self, T eps2, Lane<T, R>& l) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const T dx = l.x[r] - s.x, dy = l.y[r] - s.y, dz = l.z[r] - s.z;
+    T r2 = n3_fma(dx, dx, eps2);
+    r2 = n3_fma(dy, dy, r2);
+    r2 = n3_fma(dz, dz, r2);
+    T inv = n3_rsq(r2);
+    if (MASK && !live) inv = 0;
+    T qinv = UNIFORM ? inv : s.w * inv;
+    const T sc = qinv * (inv * inv);
+    add_term<T, KAHAN>(sc, dx, l.f[r][0], l.c[r][0]);
+    add_term<T, KAHAN>(sc, dy, l.f[r][1], l.c[r][1]);
+    add_term<T, KAHAN>(sc, dz, l.f[r][2], l.c[r][2]);
+    if (PHI) {
+      if (MASK && self == kCols * r) qinv = 0;
+      if (KAHAN) add_term<T, true>(qinv, T(1), l.f[r][3], l.c[r][3]);
+      else l.f[r][3] += qinv;
+    }
+  }
+}
+
+// The lane's share of a chunk: sources grp, grp + 64, ... of the cnt in LDS; first is the place of
+// the lane's first target among them.
+template <typename T, int R, bool KAHAN, bool PHI, bool UNIFORM, bool MASK, typename V4>
+__device__ inline void direct_chunk(const V4* src, int cnt, int grp, int64_t first, T eps2, Lane<T, R>& l) {
+  const int whole = MASK ? 0 : cnt / kStep * kStep;
+#pragma unroll 4
+  for (int k = grp; k < whole; k += kStep)
+    direct_pair<T, R, KAHAN, PHI, UNIFORM, false>(src[k], true, 0, eps2, l);
+  for (int k = whole; k < cnt; k += kStep) {
+    const bool live = k + grp < cnt;
+    direct_pair<T, R, KAHAN, PHI, UNIFORM, true>(src[live ? k + grp : 0], live, MASK ? k + grp - first : -1, eps2, l);
+  }
+}
+
+template <typename T, int R, bool KAHAN, bool PHI>
+__global__ __launch_bounds__(kThreads) void k_field_direct(const double* __restrict__ xyzq, int64_t n, double eps2d,
+                                                           double* E, double* phi) {
+  using V4 = typename N3Type<T>::V4;
+  constexpr int NC = PHI ? 4 : 3, TB = kCols * R;
+  __shared__ V4 src[kChunk];
+  double* red = reinterpret_cast<double*>(src);  // [wave][component][target], after the last chunk
+  static_assert(sizeof(double) * kWaves * 4 * TB <= sizeof(V4) * kChunk, "the block's partial sums fit");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = lane % kCols, grp = kGroups * wave + lane / kCols;
+  const T eps2 = (T)eps2d;
+  for (int64_t i0 = (int64_t)blockIdx.x * TB; i0 < n; i0 += (int64_t)gridDim.x * TB) {
+    Lane<T, R> l;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {  // lanes past the last target repeat it and store nothing
+      const int64_t i = i0 + t + kCols * r < n ? i0 + t + kCols * r : n - 1;
+      l.x[r] = (T)xyzq[i];
+      l.y[r] = (T)xyzq[n + i];
+      l.z[r] = (T)xyzq[2 * n + i];
+    }
+    double e[R][NC];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) e[r][k] = 0.0;
+    for (int64_t j0 = 0; j0 < n; j0 += kChunk) {
+      const int cnt = (int)(n - j0 < kChunk ? n - j0 : kChunk);
+      const T q0 = (T)xyzq[3 * n + j0];
+      int same = 1;
+      __syncthreads();  // the sources and sums before these are read
+      for (int k = tid; k < cnt; k += kThreads) {
+        const int64_t j = j0 + k;
+        V4 v;
+        v.x = (T)xyzq[j];
+        v.y = (T)xyzq[n + j];
+        v.z = (T)xyzq[2 * n + j];
+        v.w = (T)xyzq[3 * n + j];
+        same &= v.w == q0;
+        src[k] = v;
+      }
+      const bool uniform = __syncthreads_and(same);
+      const bool own = PHI && j0 < i0 + TB && i0 < j0 + cnt;  // the block's targets are among the sources
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) l.f[r][k] = l.c[r][k] = 0;
+      if (own) direct_chunk<T, R, KAHAN, PHI, false, true>(src, cnt, grp, i0 + t - j0, eps2, l);
+      else if (uniform) direct_chunk<T, R, KAHAN, PHI, true, false>(src, cnt, grp, 0, eps2, l);
+      else direct_chunk<T, R, KAHAN, PHI, false, false>(src, cnt, grp, 0, eps2, l);
+      const double qs = uniform && !own ? (double)q0 : 1.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) e[r][k] += (double)l.f[r][k] * qs;
+    }
+    __syncthreads();  // the last chunk is read
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        for (int o = kCols; o < 64; o <<= 1) e[r][k] += __shfl_xor(e[r][k], o, 64);
+        if (lane < kCols) red[(wave * NC + k) * TB + kCols * r + t] = e[r][k];
+      }
+    __syncthreads();
+    for (int v = tid; v < NC * TB; v += kThreads) {
+      const int k = v / TB, i = v % TB;
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) sum += red[(w * NC + k) * TB + i];
+      if (i0 + i < n) {
+        if (k < 3) E[k * n + i0 + i] = sum;
+        else phi[i0 + i] = sum;
+      }
+    }
+  }
+}
+
+template <typename T, bool KAHAN>
+hipError_t launch_direct(int64_t n, const double* xyzq, double eps2, double* E, double* phi, hipStream_t st) {
+  const int grid = (int)std::min<int64_t>((n + kCols - 1) / kCols, kGrid);
+  if (phi) k_field_direct<T, 1, KAHAN, true><<<grid, kThreads, 0, st>>>(xyzq, n, eps2, E, phi);
+  else k_field_direct<T, 1, KAHAN, false><<<grid, kThreads, 0, st>>>(xyzq, n, eps2, E, phi);
+  return hipGetLastError();
+}
+
+// ----------------------------------------------------------------------------- each pair once
+// The pair-once pass (force.hip) in its shape R = WJ = 4 (blocks of 256 charges, a thread block
+// of 4 waves per tile), reading the caller's arrays and taking the potential along.  A tile (I, J),
+// I <= J, leaves one row of sums for block I and, if I < J, one for block J.  The tiles go in
+// strips of J so that a strip's rows fit the workspace: row (I, J) of the strip from J0 sits at
+// J^2 - J0^2 + I, row (J, I) at J^2 - J0^2 + J + 1 + I, and a fold after each strip adds a charge's
+// rows in a fixed order in FP64, and to the result of the strips before.
+// VALU-bound (force.hip has the count of its instructions); the potential adds two per evaluation.
+// Measured a call, field and potential: 20,000 charges in FP32 134 us, in FP64 205 us; 50,021 in
+// FP64 without it 1117 us, in five strips, against 2699, 1040 and 5245 us before; the one-sided kernels at their best tilings take 158, 311
+// and 1843 us.
+constexpr int kPR = 4, kPB = 64 * kPR;  // targets per lane, charges per block
+
+template <typename T, bool PHI>
+struct PairLds {
+  static constexpr int NC = PHI ? 4 : 3;
+  T slice[4][4 * kN3Slice];  // a wave's sources, twice in a row
+  T jres[NC][kPB];           // sums of the block's sources
+  T ired[3][NC][kPB];        // sums of the targets by waves 1 to 3
+};
+
+template <typename T, bool PHI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 5)))
+void k_field_pairs(const double* __restrict__ xyzq, int64_t n, double eps2d, T* __restrict__ rows, int64_t J0) {
+  constexpr int NC = PHI ? 4 : 3, R = kPR;
+  constexpr T kFar = N3Type<T>::kFar;
+  __shared__ PairLds<T, PHI> s;
+  const int64_t tile = J0 * (J0 + 1) / 2 + blockIdx.x;
+  int64_t J = (int64_t)((sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);  // a guess, made exact below
+  while (J * (J + 1) / 2 > tile) --J;
+  while ((J + 1) * (J + 2) / 2 <= tile) ++J;
+  const int64_t I = tile - J * (J + 1) / 2;
+  const bool jside = I != J;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double *X = xyzq, *Y = xyzq + n, *Z = xyzq + 2 * n, *Q = xyzq + 3 * n;
+  const int64_t i0 = I * kPB, jb = J * kPB + w * 64;
+
+  // the lane's targets; places past the last charge lie so far away that they add exactly zero
+  const T qT = (T)Q[i0];
+  T xi[R], yi[R], zi[R], qi[R];
+  int same_t = 1;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = i0 + r * 64 + lane;
+    const bool live = i < n;
+    xi[r] = live ? (T)X[i] : kFar;
+    yi[r] = live ? (T)Y[i] : kFar;
+    zi[r] = live ? (T)Z[i] : kFar;
+    qi[r] = live ? (T)Q[i] : qT;
+    same_t &= qi[r] == qT;
+  }
+  const bool ut = __all(same_t);
+  const T eps2 = (T)eps2d;
+  T f[4][R], a[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    a[k] = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) f[k][r] = 0;
+  }
+  if (jb < n) {  // the wave has sources
+    const int64_t j = jb + lane;
+    const bool live = j < n;
+    const T q0 = (T)Q[jb];
+    const T x = live ? (T)X[j] : kFar, y = live ? (T)Y[j] : kFar, z = live ? (T)Z[j] : kFar;
+    const T q = live ? (T)Q[j] : T(0);
+    const bool us = __all(!live || q == q0);
+    T* sb = s.slice[w];
+    sb[lane] = sb[lane + 64] = x;
+    sb[kN3Slice + lane] = sb[kN3Slice + lane + 64] = y;
+    sb[2 * kN3Slice + lane] = sb[2 * kN3Slice + lane + 64] = z;
+    sb[3 * kN3Slice + lane] = sb[3 * kN3Slice + lane + 64] = q;
+    wave_lds_sync();
+#define LC_CHUNK(US, UT, JS)                                                                                      \
+  n3_chunk<T, R, US, UT, JS, false, PHI>(sb, lane, xi, yi, zi, qi, eps2, f[0], f[1], f[2], a[0], a[1], a[2], T(0), T(0), \
+                                         f[3], &a[3], w)
+    if (jside) {
+      if (us) {
+        if (ut) LC_CHUNK(true, true, true);
+        else LC_CHUNK(true, false, true);
+      } else {
+        if (ut) LC_CHUNK(false, true, true);
+        else LC_CHUNK(false, false, true);
+      }
+    } else {
+      if (us) LC_CHUNK(true, true, false);
+      else LC_CHUNK(false, true, false);
+    }
+#undef LC_CHUNK
+    if (us) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int r = 0; r < R; ++r) f[k][r] *= q0;
+    }
+  }
+  if (jside) {
+    // E_j = sum_i q_i (r_j - r_i) s_ij = -(reaction sum); the potential keeps its sign
+    const T qs = ut ? qT : T(1);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) s.jres[k][w * 64 + lane] = (k < 3 ? -qs : qs) * a[k];
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int r = 0; r < R; ++r) s.ired[w - 1][k][r * 64 + lane] = f[k][r];
+  }
+  __syncthreads();
+  T* row = rows + (J * J - J0 * J0 + I) * NC * kPB;
+  if (w == 0) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int l = r * 64 + lane;
+        row[k * kPB + l] = ((f[k][r] + s.ired[0][k][l]) + s.ired[1][k][l]) + s.ired[2][k][l];
+      }
+  }
+  if (jside) {
+    row += (J + 1) * NC * kPB;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) row[k * kPB + tid] = s.jres[k][tid];
+  }
+}
+
+// A strip's rows of 64 charges of a block: kFoldWaves waves take them in turn, wave 0 adds the
+// waves' sums in order.
+template <typename T, bool PHI>
+__global__ __launch_bounds__(64 * kFoldWaves) void k_field_fold(const T* __restrict__ rows, int64_t n, int64_t J0,
+                                                                int64_t J1, double* E, double* phi) {
+  constexpr int NC = PHI ? 4 : 3;
+  __shared__ double red[kFoldWaves - 1][NC][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t K = (int64_t)blockIdx.x * 64 / kPB;
+  const int l = (int)(i - K * kPB);
+  double e[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) e[k] = 0.0;
+  // partners m < K (rows of the strip only if it holds J = K), then m = max(K, J0) .. J1 - 1
+  const int64_t below = K >= J0 ? K : 0, from = K >= J0 ? K : J0;
+  const int64_t total = below + (J1 - from);
+  auto row_of = [&](int64_t v) {
+    const int64_t J = from + (v - below);
+    return rows + (v < below ? K * K - J0 * J0 + K + 1 + v : J * J - J0 * J0 + K) * NC * kPB + l;
+  };
+  int64_t v = w;
+  for (; v + 3 * kFoldWaves < total; v += 4 * kFoldWaves) {
+    T x[4][NC];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const T* r = row_of(v + u * kFoldWaves);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) x[u][k] = r[k * kPB];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) e[k] += (double)x[u][k];
+  }
+  for (; v < total; v += kFoldWaves) {
+    const T* r = row_of(v);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) e[k] += (double)r[k * kPB];
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) red[w - 1][k][lane] = e[k];
+  }
+  __syncthreads();
+  if (w == 0 && i < n) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      for (int q = 0; q < kFoldWaves - 1; ++q) e[k] += red[q][k][lane];
+      double* out = k < 3 ? E + k * n + i : phi + i;
+      *out = K < J0 ? *out + e[k] : e[k];  // an earlier strip has begun the sum
+    }
+  }
+}
+
+// Rows a strip may hold, and the end of the strip that starts at J0 (J1^2 - J0^2 rows).
+template <typename T, bool PHI>
+int64_t strip_rows() {
+  return (int64_t)(LC_FIELD_STATIC_MAX_BYTES / (sizeof(T) * (PHI ? 4 : 3) * kPB));
+}
+
+template <typename T, bool PHI>
+hipError_t launch_pairs(int64_t n, const double* xyzq, double eps2, double* E, double* phi, void* work,
+                        hipStream_t st) {
+  const int64_t nb = (n + kPB - 1) / kPB, cap = strip_rows<T, PHI>();
+  for (int64_t J0 = 0; J0 < nb;) {
+    int64_t J1 = J0;
+    while (J1 < nb && (J1 + 1) * (J1 + 1) - J0 * J0 <= cap) ++J1;
+    const int tiles = (int)(J1 * (J1 + 1) / 2 - J0 * (J0 + 1) / 2);
+    k_field_pairs<T, PHI><<<tiles, 256, 0, st>>>(xyzq, n, eps2, (T*)work, J0);
+    // blocks from J1 on have no rows in this strip
+    const int64_t last = std::min<int64_t>(n, J1 * kPB);
+    k_field_fold<T, PHI><<<(int)((last + 63) / 64), 64 * kFoldWaves, 0, st>>>((const T*)work, n, J0, J1, E, phi);
+    J0 = J1;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Each pair once from 3584 charges (14 blocks) on, as long as a strip can hold the rows of one J
+// (up to about a million charges).  Below, 105 tiles or fewer leave most of the chip idle: 3000
+// charges take 17 to 22 us each pair once and 14 to 19 us direct, 4099 take 18 to 24 us against 20
+// to 41 us.  Kahan sums have no form that takes each pair once.
+constexpr int64_t kPairsFrom = 3584;
+bool field_pairs(int precision, int64_t n) {
+  if (precision == LC_FP32_KAHAN || n < kPairsFrom) return false;
+  const int64_t nb = (n + kPB - 1) / kPB;
+  return 2 * nb - 1 <= (precision == LC_FP64 ? strip_rows<double, true>() : strip_rows<float, true>());
+}
+
+size_t field_default_bytes(int precision, int64_t n) {
+  if (!field_pairs(precision, n)) return 0;
+  const int64_t nb = (n + kPB - 1) / kPB;
+  const size_t row = (precision == LC_FP64 ? sizeof(double) : sizeof(float)) * 4 * kPB;
+  return std::min<size_t>(LC_FIELD_STATIC_MAX_BYTES, (size_t)nb * (size_t)nb * row);
+}
+
+hipError_t launch_field_default(int precision, int64_t n, const double* xyzq, double eps2, double* E, double* phi,
+                                void* work, size_t work_bytes, hipStream_t st) {
+  if (n == 0) return hipSuccess;
+  if (field_pairs(precision, n) && work_bytes >= field_default_bytes(precision, n)) {
+    if (precision == LC_FP64)
+      return phi ? launch_pairs<double, true>(n, xyzq, eps2, E, phi, work, st)
+                 : launch_pairs<double, false>(n, xyzq, eps2, E, phi, work, st);
+    return phi ? launch_pairs<float, true>(n, xyzq, eps2, E, phi, work, st)
+               : launch_pairs<float, false>(n, xyzq, eps2, E, phi, work, st);
+  }
+  if (precision == LC_FP64) return launch_direct<double, false>(n, xyzq, eps2, E, phi, st);
+  if (precision == LC_FP32_KAHAN) return launch_direct<float, true>(n, xyzq, eps2, E, phi, st);
+  return launch_direct<float, false>(n, xyzq, eps2, E, phi, st);
+}
+
+}  // namespace lc
