@@ -958,8 +958,20 @@ FieldWs carve_field_ws(void* work, int precision, int64_t n, const ForceTiling& 
   return w;
 }
 
-__global__ void k_field_setup(FieldWs w, int64_t n, int i_blocks, int tiles) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
+// The source records, and in the first thread the one cluster's tables.
+template <typename Src>
+__global__ __launch_bounds__(kBlock) void k_field_setup(FieldWs w, const double* xyzq, int64_t n, int i_blocks,
+                                                        int tiles) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) {
+    Src v;
+    v.x = xyzq[i];
+    v.y = xyzq[n + i];
+    v.z = xyzq[2 * n + i];
+    v.w = xyzq[3 * n + i];
+    ((Src*)w.src)[i] = v;
+  }
+  if (i == 0) {
     ClusterParams cp = {};
     cp.off = 0;
     cp.cap = n;
@@ -979,18 +991,6 @@ __global__ void k_field_setup(FieldWs w, int64_t n, int i_blocks, int tiles) {
   }
 }
 
-template <typename Src>
-__global__ void k_pack_sources(const double* xyzq, int64_t n, Src* out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  Src v;
-  v.x = xyzq[i];
-  v.y = xyzq[n + i];
-  v.z = xyzq[2 * n + i];
-  v.w = xyzq[3 * n + i];
-  out[i] = v;
-}
-
 __global__ void k_sum_partials(const double* part, int64_t n, int S, double* E, double* phi) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -1008,23 +1008,48 @@ __global__ void k_sum_partials(const double* part, int64_t n, int S, double* E, 
   if (phi) phi[i] = p;
 }
 
-// Field of the standalone call from pair-once rows (M = nb rows per block).
+// Field of the standalone call from pair-once rows (M = nb rows per block): a block of kFoldWaves
+// waves takes 64 slots, wave w the rows m = w, w + kFoldWaves, ..., four loads of a component in
+// flight at a time; wave 0 adds the waves' sums in order.
 template <typename Tr>
-__global__ void k_sum_n3(const Tr* rows, int64_t n, int B, double* E) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t K = i / B, l = i - K * B;
+__global__ __launch_bounds__(64 * kFoldWaves) void k_sum_n3(const Tr* rows, int64_t n, int B, double* E) {
+  __shared__ double red[kFoldWaves - 1][3][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
   const int64_t nb = (n + B - 1) / B;
-  const Tr* r = rows + K * nb * 3 * B + l;
-  double e0 = 0.0, e1 = 0.0, e2 = 0.0;
-  for (int64_t m = 0; m < nb; ++m, r += 3 * (int64_t)B) {
-    e0 += (double)r[0];
-    e1 += (double)r[B];
-    e2 += (double)r[2 * B];
+  double e[3] = {0.0, 0.0, 0.0};
+  if (i < n) {
+    const int64_t K = i / B, l = i - K * B;
+    const int64_t step = 3 * (int64_t)B * kFoldWaves;
+    const Tr* r = rows + (K * nb + w) * 3 * B + l;
+    int64_t m = w;
+    for (; m + 3 * kFoldWaves < nb; m += 4 * kFoldWaves, r += 4 * step) {
+      Tr v[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[u][k] = r[u * step + k * B];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) e[k] += (double)v[u][k];
+    }
+    for (; m < nb; m += kFoldWaves, r += step)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) e[k] += (double)r[k * B];
   }
-  E[i] = e0;
-  E[n + i] = e1;
-  E[2 * n + i] = e2;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (w > 0) red[w - 1][k][lane] = e[k];
+  __syncthreads();
+  if (w == 0 && i < n) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      for (int q = 0; q < kFoldWaves - 1; ++q) e[k] += red[q][k][lane];
+      E[k * n + i] = e[k];
+    }
+  }
 }
 
 }  // namespace
@@ -1157,10 +1182,9 @@ hipError_t launch_field_standalone(int precision, int64_t n, const double* xyzq,
   const int ib = (int)((n + TI - 1) / TI);
   const int64_t tiles = ft.newton3 ? (int64_t)ib * (ib + 1) / 2 : (int64_t)ib * ft.S;
   if (tiles > std::numeric_limits<int32_t>::max()) return hipErrorInvalidValue;
-  k_field_setup<<<1, 64, 0, st>>>(w, n, ib, (int)tiles);
   const int pb = (int)((n + kBlock - 1) / kBlock);
-  if (precision == LC_FP64) k_pack_sources<double4><<<pb, kBlock, 0, st>>>(xyzq, n, (double4*)w.src);
-  else k_pack_sources<float4><<<pb, kBlock, 0, st>>>(xyzq, n, (float4*)w.src);
+  if (precision == LC_FP64) k_field_setup<double4><<<pb, kBlock, 0, st>>>(w, xyzq, n, ib, (int)tiles);
+  else k_field_setup<float4><<<pb, kBlock, 0, st>>>(w, xyzq, n, ib, (int)tiles);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   TileMap map{w.ints, w.ints + 2, w.cp, w.dyn, w.ints + 3, w.ints + 4, 1};
@@ -1174,16 +1198,17 @@ hipError_t launch_field_standalone(int precision, int64_t n, const double* xyzq,
   }
   if (ft.newton3) {
     if (phi) return hipErrorInvalidValue;
+    const int fb = (int)((n + 63) / 64);
     if (precision == LC_FP64) {
       N3Args<double> a{(const double4*)w.src, (double*)w.part, ib, eps2, ft.persistent, map, StepBegin{}};
       e = launch_n3(ft, a, grid, false, st);
       if (e != hipSuccess) return e;
-      k_sum_n3<double><<<pb, kBlock, 0, st>>>((const double*)w.part, n, TI, E);
+      k_sum_n3<double><<<fb, 64 * kFoldWaves, 0, st>>>((const double*)w.part, n, TI, E);
     } else {
       N3Args<float> a{(const float4*)w.src, (float*)w.part, ib, eps2, ft.persistent, map, StepBegin{}};
       e = launch_n3(ft, a, grid, false, st);
       if (e != hipSuccess) return e;
-      k_sum_n3<float><<<pb, kBlock, 0, st>>>((const float*)w.part, n, TI, E);
+      k_sum_n3<float><<<fb, 64 * kFoldWaves, 0, st>>>((const float*)w.part, n, TI, E);
     }
     return hipGetLastError();
   }
