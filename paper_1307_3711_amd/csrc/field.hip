@@ -59,10 +59,17 @@ __device__ inline void direct_pair(const V4 s, bool live, int64_t self, T eps2, 
     T r2 = n3_fma(dx, dx, eps2);
     r2 = n3_fma(dy, dy, r2);
     r2 = n3_fma(dz, dz, r2);
-    T inv = n3_rsq(r2);
-    if (MASK && !live) inv = 0;
-    T qinv = UNIFORM ? inv : s.w * inv;
-    const T sc = qinv * (inv * inv);
+    T qinv = 0, sc;
+    if (PHI || sizeof(T) == 4) {
+      T inv = n3_rsq(r2);
+      if (MASK && !live) inv = 0;
+      qinv = UNIFORM ? inv : s.w * inv;
+      sc = qinv * (inv * inv);
+    } else {
+      sc = n3_cubed(r2);
+      if (MASK && !live) sc = 0;
+      if (!UNIFORM) sc *= s.w;
+    }
     add_term<T, KAHAN>(sc, dx, l.f[r][0], l.c[r][0]);
     add_term<T, KAHAN>(sc, dy, l.f[r][1], l.c[r][1]);
     add_term<T, KAHAN>(sc, dz, l.f[r][2], l.c[r][2]);

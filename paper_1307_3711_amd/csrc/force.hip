@@ -374,9 +374,14 @@ __device__ void tile_f64(const ForceArgs<double4>& a, int t, double4* lds) {
           double r2 = __builtin_fma(dx, dx, eps2);
           r2 = __builtin_fma(dy, dy, r2);
           r2 = __builtin_fma(dz, dz, r2);
-          const double inv = rsq64(r2);
-          double qinv = sj.w * inv;
-          const double sc = qinv * (inv * inv);
+          double qinv = 0.0, sc;
+          if (PHI) {
+            const double inv = rsq64(r2);
+            qinv = sj.w * inv;
+            sc = qinv * (inv * inv);
+          } else {
+            sc = sj.w * rsq64_cubed(r2);
+          }
           ex[r] = __builtin_fma(sc, dx, ex[r]);
           ey[r] = __builtin_fma(sc, dy, ey[r]);
           ez[r] = __builtin_fma(sc, dz, ez[r]);

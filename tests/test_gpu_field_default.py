@@ -85,3 +85,21 @@ def test_default_field_in_the_one_sided_workspace(precision):
     s1, _ = _scales(x, q, EPS2, idx)
     u = 1e-12 if precision == 0 else 64.0 * U32
     assert np.all(np.abs((E - E2).cpu().numpy().T[idx]) <= 2.0 * u * s1[:, None])
+
+
+@pytest.mark.parametrize("scale", [1e-60, 1e-20, 1e20, 1e90])
+@pytest.mark.parametrize("n,tuning", [(300, None), (3600, None), (300, dict(R=4, WJ=4, newton3=1)), (300, dict(R=2, S=2))])
+def test_fp64_field_at_any_length_scale(n, tuning, scale):
+    """E scales as q / length^2: lengths and softening scaled by powers of ten leave the relative
+    rounding of every pair term alone."""
+    import torch
+    import paper_1307_3711_amd as lc
+    x, q = _particles(n, 3)
+    s1, _ = _scales(x, q, EPS2, np.arange(0, n, 29))
+    out = []
+    for f in (1.0, scale):
+        xyzq = torch.tensor(np.concatenate([f * x.T, q[None, :]], axis=0), dtype=torch.float64, device="cuda").contiguous()
+        t = lc.make_tuning(**tuning) if tuning else None
+        E, _ = lc.field(xyzq, EPS2 * f * f, precision="fp64", want_phi=False, tuning=t)
+        out.append((E.cpu().numpy() * f) * f)
+    assert np.all(np.abs(out[1] - out[0]).T[::29] <= 2e-12 * s1[:, None])
