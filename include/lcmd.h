@@ -156,7 +156,8 @@ typedef struct {
   double lotz_a;              /* Lotz constant a (cm^2 eV^2)                            */
 } lc_cluster;
 
-/* Tiling of the Coulomb kernel (the autotuner's search space).  Zeros mean "default". */
+/* Tiling of the Coulomb kernel (the autotuner's search space).  Zeros mean "default"; all zeros
+ * (as without lc_set_tuning): a one-sided tiling chosen from the particle counts. */
 typedef struct {
   int32_t targets_per_lane;   /* R: 1, 2, 4 or 8 register-blocked targets per lane      */
   int32_t waves_per_target;   /* WJ: 1, 2 or 4 waves of a block share targets and split  */
