@@ -82,15 +82,17 @@ __device__ inline int weight_row(int tc, int m) { return unit_of(4 * tc + (m & 3
 // parameters it updates, with their Adam moments, in registers over all steps.  What crosses
 // waves goes through LDS, four barriers a step.
 // Bound by the VALU issue of one compute unit (the two SiLUs and their derivatives of 256 rows are
-// most of it).  Measured at 256 rows: 24.2 us a step, against 200 us with four waves that kept
-// every activation in global memory; with expf's range checks, the general division and the first
-// layer on the VALU 29 us.  Every sum keeps its order and every operation its rounding, so trained
-// weights are the same bits in all three.
+// most of it: 10.8 us; the sums over rows 3.9, Adam 1.2).  Measured at 256 rows: 17.1 us a step,
+// against 200 us with four waves that kept every activation in global memory; with the sums over
+// rows on one LDS read per row 24.2 us, and with expf's range checks, the general division and the
+// first layer on the VALU 29 us.  Every sum keeps its order and every operation its rounding, so
+// trained weights are the same bits in all of these.  The transposing LDS read in place of the
+// transposed arrays' 2-byte writes was no faster (18.3 and 19.1 us).
 constexpr int kTrainWaves = 16;
 constexpr int kTrainThreads = 64 * kTrainWaves;
 constexpr int kColPad = kMaxBatch + 8;  // entries of a transposed row: 16-byte reads of 16 rows meet no bank twice
 constexpr int kWPad = kH + 8;           // likewise for rows of units
-constexpr int kFPad = kH + 1;
+constexpr int kFPad = kMaxBatch + 4;    // likewise for FP32 entries
 
 struct TrainLds {
   __bf16 w2[kH][kWPad];      // W2[n][k]
@@ -100,14 +102,14 @@ struct TrainLds {
   alignas(16) float b1[kH];
   float b2[kH];
   float b3[kOut];
-  float xs[kMaxBatch][kIn];  // standardized, BF16-rounded inputs
-  float dy[kMaxBatch][kOut];
+  alignas(16) float xs[kIn][kMaxBatch];  // standardized, BF16-rounded inputs
+  float dy[kOut][kMaxBatch];
   float4 corr[64];           // 1 - beta1^t, 1 - beta2^t and their reciprocals, of 64 steps
   float loss[kTrainWaves];
-  float f[kMaxBatch][kFPad]; // hidden-2 gradient, then hidden-1 gradient
-  union {
-    __bf16 h2[kMaxBatch][kWPad];  // hidden-2 activations, until their sums are taken
-    struct {                      // the operands of dW2, [unit][row]
+  alignas(16) float f[kH][kFPad];  // [unit][row]: hidden-2 gradient, then hidden-1 gradient
+  union {                          // [unit][row]
+    __bf16 h2t[kH][kColPad];       // hidden-2 activations, until their sums are taken
+    struct {                       // the operands of dW2
       __bf16 h1t[kH][kColPad];
       __bf16 d2t[kH][kColPad];
     };
@@ -165,25 +167,53 @@ __device__ inline void adam(float g, float lr, float beta1, float beta2, float e
   p -= lr * div_by(m, c.x, c.z) / (sqrtf(div_by(v, c.y, c.w)) + eps);
 }
 
-// Sum over the B rows (a multiple of 32) in row order, add(operands of a row, sum so far): the
-// operands of 16 rows are loaded while the 16 rows before them are added.
-template <typename L, typename A>
-__device__ inline float row_chain(int B, L load, A add) {
-  decltype(load(0)) u[16], v[16];
+// Sums over the B rows (a multiple of 32) in row order, of f[r] or of f[r] g[r]: the rows of a
+// column are neighbours in LDS, so eight come with two 16-byte reads (one of BF16), ahead of the
+// additions of the eight before.
+struct Eight {
+  f32x4 a, b;
+};
+__device__ inline Eight load_eight(const float* p) { return {*(const f32x4*)p, *(const f32x4*)(p + 4)}; }
+__device__ inline Eight load_eight(const __bf16* p) {
+  const bf16x8 v = *(const bf16x8*)p;
+  Eight o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    o.a[i] = (float)v[i];
+    o.b[i] = (float)v[4 + i];
+  }
+  return o;
+}
+
+template <typename T>
+__device__ inline float column_dot(int B, const T* f, const float* g) {
   float sum = 0.f;
+  Eight u = load_eight(f), v = load_eight(g);
+#pragma unroll 4
+  for (int r = 8; r <= B; r += 8) {
+    const int next = r < B ? r : 0;  // the last one is not used
+    const Eight u1 = load_eight(f + next), v1 = load_eight(g + next);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) u[i] = load(i);
-#pragma unroll 1
-  for (int r = 0; r < B; r += 32) {
+    for (int i = 0; i < 4; ++i) sum = __builtin_fmaf(v.a[i], u.a[i], sum);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = load(r + 16 + i);
+    for (int i = 0; i < 4; ++i) sum = __builtin_fmaf(v.b[i], u.b[i], sum);
+    u = u1;
+    v = v1;
+  }
+  return sum;
+}
+
+__device__ inline float column_add(int B, const float* f) {
+  float sum = 0.f;
+  Eight u = load_eight(f);
+#pragma unroll 4
+  for (int r = 8; r <= B; r += 8) {
+    const Eight u1 = load_eight(f + (r < B ? r : 0));
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum = add(u[i], sum);
-    const int next = r + 32 < B ? r + 32 : 0;  // the last one is not used
+    for (int i = 0; i < 4; ++i) sum += u.a[i];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) u[i] = load(next + i);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sum = add(v[i], sum);
+    for (int i = 0; i < 4; ++i) sum += u.b[i];
+    u = u1;
   }
   return sum;
 }
@@ -266,7 +296,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
       for (int o = 0; o < kOut; ++o) ty[o] = (yr[o] - ymu[o]) / ysd[o];
       if (step + 1 < steps) load_row(next);
       if (step + 2 < steps) next = row_index(step + 2);
-      w.xs[row][g] = x;
+      w.xs[g][row] = x;
       // layer 1: z1 = W1 x + b1 on the FP32 matrix units, whose sum over the four inputs rounds as a
       // chain of fused multiply-adds does
 #pragma unroll
@@ -298,11 +328,10 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
           const float sg = sigmoid_train(z);
           e2[q] = sg * (1.0f + z * (1.0f - sg));
           h2[q >> 3][q & 7] = (__bf16)(z * sg);
+          w.h2t[unit_of(q, g)][row] = h2[q >> 3][q & 7];
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      *(bf16x8*)&w.h2[row][8 * g] = h2[0];
-      *(bf16x8*)&w.h2[row][32 + 8 * g] = h2[1];
       // layer 3: y = W3 h2 + b3, summed in unit order: each lane group adds its eight units and
       // hands the sum to the next group
       float y[kOut] = {w.b3[0], w.b3[1]};
@@ -328,7 +357,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
       }
       if (g == 0) {
 #pragma unroll
-        for (int o = 0; o < kOut; ++o) w.dy[row][o] = dy[o];
+        for (int o = 0; o < kOut; ++o) w.dy[o][row] = dy[o];
       }
 #pragma unroll
       for (int o = 1; o < 16; o <<= 1) l += __shfl_xor(l, o, 64);
@@ -340,7 +369,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
         const float gr = __builtin_fmaf(w.w3[1][u], dy[1], w.w3[0][u] * dy[0]);
         const float d = gr * e2[q];
         d2[q >> 3][q & 7] = (__bf16)d;
-        w.f[row][u] = d;
+        w.f[u][row] = d;
         if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
       // hidden-1 gradient: dz1 = (W2^T dz2) SiLU'(z1)
@@ -358,14 +387,12 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
     // the sums over rows of hidden-2 quantities: dW3[o][j] = sum_r dy[r][o] h2[r][j],
     // db2[j] = sum_r dz2[r][j], db3[o] = sum_r dy[r][o]
     float gs = 0.f;
-    const auto plus = [](float v, float sum) { return sum + v; };
-    const auto product = [](float2 v, float sum) { return __builtin_fmaf(v.x, v.y, sum); };
     if (wave < 2) {
-      gs = row_chain(B, [&](int r) { return make_float2(w.dy[r][wave], (float)w.h2[r][lane]); }, product);
+      gs = column_dot(B, w.h2t[lane], w.dy[wave]);
     } else if (wave == 2) {
-      gs = row_chain(B, [&](int r) { return w.f[r][lane]; }, plus);
+      gs = column_add(B, w.f[lane]);
     } else if (wave == 3 && lane < kOut) {
-      gs = row_chain(B, [&](int r) { return w.dy[r][lane]; }, plus);
+      gs = column_add(B, w.dy[lane]);
     } else if (wave == kTrainWaves - 1 && lane == 0 && loss_out) {
       float l = 0.f;
       for (int q = 0; q < nw; ++q) l += w.loss[q];
@@ -376,7 +403,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int u = unit_of(q, g);
-        w.f[row][u] = e1[q];
+        w.f[u][row] = e1[q];
         w.h1t[u][row] = h1[q >> 3][q & 7];
         w.d2t[u][row] = d2[q >> 3][q & 7];
       }
@@ -384,11 +411,8 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
     __syncthreads();
 
     // dW1[j][k] = sum_r dz1[r][j] x[r][k], db1[j] = sum_r dz1[r][j]
-    if (wave >= 4 && wave < 8) {
-      gs = row_chain(B, [&](int r) { return make_float2(w.f[r][lane], w.xs[r][wave - 4]); }, product);
-    } else if (wave == 8) {
-      gs = row_chain(B, [&](int r) { return w.f[r][lane]; }, plus);
-    }
+    if (wave >= 4 && wave < 8) gs = column_dot(B, w.f[lane], w.xs[wave - 4]);
+    else if (wave == 8) gs = column_add(B, w.f[lane]);
     // dW2[n][k] = sum_r dz2[r][n] h1[r][k]: the wave's 16 x 16 tile over the minibatch
     f32x4 gw = {0.f, 0.f, 0.f, 0.f};
     for (int kk = 0; kk < B; kk += 32)
