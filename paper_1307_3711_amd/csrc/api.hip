@@ -384,9 +384,12 @@ int choose_splits(const lc_sim* s, const ForceTiling& ft) {
 
 // The one-sided tiling of a handle whose caller asked for none, from the particle counts (with
 // ionization the capacities, so that a run saved and loaded keeps its tiling).
-// FP32: default_tiling's splits and segments, with one target per lane instead of four and (open
-// boundaries, no Kahan sums) the sources through the scalar unit: four times the blocks, and every target's sum in the same
-// order, so the same bits.  A pass over 3000 macroparticles: 27.7 -> 10.9 us.
+// FP32: default_tiling's splits and segments with one target per lane instead of four: four times
+// the blocks, and every target's sum in the same order, so the same bits.  A pass over 3000
+// macroparticles: 27.7 -> 10.0 us.  Sources come from LDS, below 2048 macroparticles through the
+// scalar unit (a step of 1000: 13.4 against 14.1 us; of 3000 17.5 against 16.8, of 20,000 144
+// against 131); Kahan sums would meet a segment's padding in LDS, and a periodic pass factors equal
+// charges out of whole segments only there, so both stay there.
 // FP64: one target per lane, the block's four waves sharing its 64 targets, and enough splits for
 // about 4096 blocks (four waves for every SIMD), at most 16 and at least 8 where clusters are large
 // enough for the finer tail to pay, none below 128 sources; a pass over 36 clusters of 80 to 1000
@@ -406,9 +409,7 @@ ForceTiling auto_tiling(const lc_sim* s) {
   if (s->cfg.precision != LC_FP64) {
     ft.S = choose_splits(s, ft);
     ft.R = 1;
-    // From LDS, a periodic pass factors equal charges out of whole segments only, and Kahan sums
-    // meet the padding of a segment: both stay there.
-    ft.scalar_src = s->cfg.precision == LC_FP32_ACC64 && s->cfg.boundary == LC_OPEN ? 1 : 0;
+    ft.scalar_src = s->cfg.precision == LC_FP32_ACC64 && s->cfg.boundary == LC_OPEN && typical < 2048.0 ? 1 : 0;
     return ft;
   }
   int64_t S = std::min<int64_t>(16, (4096 + blocks - 1) / blocks);
