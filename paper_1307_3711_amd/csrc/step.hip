@@ -707,12 +707,55 @@ __device__ inline double laser_strength(const ClusterParams& cp, const ClusterDy
                                           : fabs(d.laser_e);
 }
 
-// Flag every ion whose uniform draw alpha in (0,1] falls below P = 1 - exp(-nu dt), nu the
-// ADK rate at the driving field (plus the collisional rate inside the cluster sphere); count
-// flags per ion block.  With the laser-only field the rate depends on the charge state alone,
-// so the first 32 threads of a block evaluate P for every charge state (outside and inside the
-// sphere) once, with the same arithmetic as the per-ion path of LC_LOCAL.  An ion whose P is
-// exactly 0 cannot ionize (alpha > 0) and takes no draw.
+// Ionization probabilities of a cluster's charge states this step, outside (p[0]) and inside (p[1])
+// the collisional sphere, with the laser-only field: the rate then depends on the charge state alone,
+// so threads 0 .. 31 of a block evaluate P = 1 - exp(-nu dt) for every state once, with the same
+// arithmetic as ion_flag for LC_LOCAL.
+__device__ inline void ionize_table(const RunConst& rc, const ClusterParams& cp, const ClusterDyn& d,
+                                    double (*p)[LC_MAX_Z]) {
+  if (threadIdx.x < 2 * LC_MAX_Z) {
+    const int z = threadIdx.x % LC_MAX_Z, inside = threadIdx.x / LC_MAX_Z;
+    double P = 0.0;
+    if (z < cp.z_max && cp.adk_ok[z]) {
+      double nu = adk_nu(cp, z, laser_strength(cp, d) * cp.field_au);
+      if (inside) nu += d.ci_nu[z];
+      P = -expm1(-nu * rc.dt);
+    }
+    p[inside][z] = P;
+  }
+}
+
+// Whether ion li (slot g) of cluster c ionizes in step n: its uniform draw alpha in (0,1] falls below
+// P = 1 - exp(-nu dt), nu the ADK rate at the driving field (plus the collisional rate inside the
+// cluster sphere).  An ion whose P is exactly 0 cannot ionize (alpha > 0) and takes no draw.
+__device__ inline int ion_flag(const DevState& s, const RunConst& rc, const FieldLayout& fl, const ClusterParams& cp,
+                               const ClusterDyn& d, const double (*table)[LC_MAX_Z], int c, int64_t li, int64_t g,
+                               int64_t n) {
+  const int zc = s.Z[g];
+  if (!(zc >= 0 && zc < cp.z_max && cp.adk_ok[zc])) return 0;
+  bool inside = false;
+  if (rc.collisional) {
+    const double x = s.x[g], y = s.y[g], z = s.z[g];
+    inside = x * x + y * y + z * z < cp.ci_r2;
+  }
+  double P;
+  if (!rc.ofi_local) {
+    P = table[inside ? 1 : 0][zc];
+  } else {
+    double ex, ey, ez;
+    field_sum(s, rc, fl, g, ex, ey, ez);
+    ex += d.laser_e;
+    ey += d.laser_ey;
+    double nu = adk_nu(cp, zc, sqrt(ex * ex + ey * ey + ez * ez) * cp.field_au);
+    if (inside) nu += d.ci_nu[zc];
+    P = -expm1(-nu * rc.dt);
+  }
+  if (!(P > 0.0)) return 0;
+  const U64x4 r = philox(rc.seed, (uint64_t)c, (uint64_t)li, (uint64_t)n, kPurposeAlpha, 0);
+  return (unit_interval(r.v[0]) < P) ? 1 : 0;
+}
+
+// Flags of a block's 256 ions, and their count.
 template <int PREC>
 __global__ __launch_bounds__(kBlock) void k_ionize_check(DevState s, RunConst rc, FieldLayout fl, int64_t k) {
   __shared__ double sh_p[2][LC_MAX_Z];
@@ -723,48 +766,14 @@ __global__ __launch_bounds__(kBlock) void k_ionize_check(DevState s, RunConst rc
   const int b = ibk - cp.ion_block0;
   const int64_t li = (int64_t)b * kBlock + threadIdx.x;
   if (b == 0 && threadIdx.x == 0) d.n_base = d.n_cur;
-  const bool table = !rc.ofi_local;  // uniform over the launch
-  if (table) {
-    if (threadIdx.x < 2 * LC_MAX_Z) {
-      const int z = threadIdx.x % LC_MAX_Z, inside = threadIdx.x / LC_MAX_Z;
-      double P = 0.0;
-      if (z < cp.z_max && cp.adk_ok[z]) {
-        double nu = adk_nu(cp, z, laser_strength(cp, d) * cp.field_au);
-        if (inside) nu += d.ci_nu[z];
-        P = -expm1(-nu * rc.dt);
-      }
-      sh_p[inside][z] = P;
-    }
+  if (!rc.ofi_local) {  // uniform over the launch
+    ionize_table(rc, cp, d, sh_p);
     __syncthreads();
   }
   int flag = 0;
   if (d.active && li < cp.n_ion) {
     const int64_t g = cp.off + li;
-    const int zc = s.Z[g];
-    if (zc >= 0 && zc < cp.z_max && cp.adk_ok[zc]) {
-      bool inside = false;
-      if (rc.collisional) {
-        const double x = s.x[g], y = s.y[g], z = s.z[g];
-        inside = x * x + y * y + z * z < cp.ci_r2;
-      }
-      double P;
-      if (table) {
-        P = sh_p[inside ? 1 : 0][zc];
-      } else {
-        double ex, ey, ez;
-        field_sum(s, rc, fl, g, ex, ey, ez);
-        ex += d.laser_e;
-        ey += d.laser_ey;
-        double nu = adk_nu(cp, zc, sqrt(ex * ex + ey * ey + ez * ez) * cp.field_au);
-        if (inside) nu += d.ci_nu[zc];
-        P = -expm1(-nu * rc.dt);
-      }
-      if (P > 0.0) {
-        const int64_t n = *s.step + k;
-        const U64x4 r = philox(rc.seed, (uint64_t)c, (uint64_t)li, (uint64_t)n, kPurposeAlpha, 0);
-        flag = (unit_interval(r.v[0]) < P) ? 1 : 0;
-      }
-    }
+    flag = ion_flag(s, rc, fl, cp, d, sh_p, c, li, g, *s.step + k);
     s.flag[g] = flag;
   }
   const int cnt = __syncthreads_count(flag);
@@ -820,6 +829,58 @@ __global__ __launch_bounds__(1024) void k_ionize_scan(DevState s, int n_blocks) 
   }
 }
 
+// The electron of flagged ion li (slot cp.off + li) in local slot e < cap: next to the ion's new
+// position with its momentum; the ion's charge goes up.
+template <int PREC>
+__device__ inline void spawn_electron(const DevState& s, const RunConst& rc, const ClusterParams& cp, int c, int64_t li,
+                                      int64_t e, int64_t n) {
+  const int64_t gi = cp.off + li;
+  const int64_t ge = cp.off + e;
+  const U64x4 r = philox(rc.seed, (uint64_t)c, (uint64_t)li, (uint64_t)n, kPurposeDirection, 0);
+  const double ct = 2.0 * unit_interval(r.v[0]) - 1.0;
+  const double ph = 2.0 * M_PI * unit_interval(r.v[1]);
+  const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
+  double xe = s.x[gi] + cp.delta * st * cos(ph);
+  double ye = s.y[gi] + cp.delta * st * sin(ph);
+  double ze = s.z[gi] + cp.delta * ct;
+  if (periodic_at(rc, rc.t0 + (double)n * rc.dt)) {
+    xe = wrap_box(xe, cp.box);
+    ye = wrap_box(ye, cp.box);
+    ze = wrap_box(ze, cp.box);
+  }
+  const double ux = s.ux[gi], uy = s.uy[gi], uz = s.uz[gi];
+  s.x[ge] = xe; s.y[ge] = ye; s.z[ge] = ze;
+  s.ux[ge] = ux; s.uy[ge] = uy; s.uz[ge] = uz;
+  s.Z[ge] = -1;
+  s.wl[ge] = 0.0;
+  s.wc[ge] = 0.0;
+  s.wsp[ge] = cp.weight * gm1(ux, uy, uz);
+  const bool grid = periodic_at(rc, rc.t0 + (double)(n + 1) * rc.dt);  // records for step n + 1
+  write_source(s, PREC, grid, cp.box, ge, xe, ye, ze, -cp.kw);
+  const int znew = s.Z[gi] + 1;
+  s.Z[gi] = (int8_t)znew;
+  write_source(s, PREC, grid, cp.box, gi, s.x[gi], s.y[gi], s.z[gi], cp.kw * (double)znew);
+}
+
+// Counters of a cluster after `total` of its ions ionized in a step that began with n_base particles.
+__device__ inline void count_spawns(const DevState& s, const ClusterParams& cp, ClusterDyn& d, int64_t n_base,
+                                    int64_t total) {
+  const int64_t room = cp.cap - n_base;
+  const int64_t fit = total < room ? total : room;
+  d.dropped += total - fit;
+  d.events += fit;
+  d.n_cur = n_base + fit;
+  if (total > fit) atomicOr(s.err, kFlagCapacity);
+}
+
+// Place of this thread among the flagged threads of its wave, and the wave's count.
+__device__ inline int flag_rank(int flag, int& count) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t ball = __ballot(flag);
+  count = __popcll(ball);
+  return __popcll(ball & ((lane == 0) ? 0ULL : (~0ULL >> (64 - lane))));
+}
+
 // Spawn one electron per flagged ion at slot n_base + (rank of the ion among this step's
 // flagged ions, ascending ion index), next to the ion's new position with its momentum.
 // The rank base of a block (flags of the cluster's earlier blocks) comes from the scan kernel
@@ -850,55 +911,55 @@ __global__ __launch_bounds__(kBlock) void k_ionize_spawn(DevState s, RunConst rc
     base = (int64_t)sh_pre[0] + sh_pre[1] + sh_pre[2] + sh_pre[3];
   }
   const int flag = (li < cp.n_ion) ? s.flag[cp.off + li] : 0;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint64_t ball = __ballot(flag);
-  const int below = __popcll(ball & ((lane == 0) ? 0ULL : (~0ULL >> (64 - lane))));
-  if (lane == 0) sh_wave[wv] = __popcll(ball);
+  const int wv = threadIdx.x >> 6;
+  int count;
+  const int below = flag_rank(flag, count);
+  if ((threadIdx.x & 63) == 0) sh_wave[wv] = count;
   __syncthreads();
   int wave_off = 0;
   for (int q = 0; q < wv; ++q) wave_off += sh_wave[q];
   const int64_t n_base = d.n_base;
-  const int64_t rank = base + wave_off + below;
-  if (flag) {
-    const int64_t e = n_base + rank;
-    if (e < cp.cap) {
-      const int64_t gi = cp.off + li;
-      const int64_t ge = cp.off + e;
-      const int64_t n = *s.step + k;
-      const U64x4 r = philox(rc.seed, (uint64_t)c, (uint64_t)li, (uint64_t)n, kPurposeDirection, 0);
-      const double ct = 2.0 * unit_interval(r.v[0]) - 1.0;
-      const double ph = 2.0 * M_PI * unit_interval(r.v[1]);
-      const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
-      double xe = s.x[gi] + cp.delta * st * cos(ph);
-      double ye = s.y[gi] + cp.delta * st * sin(ph);
-      double ze = s.z[gi] + cp.delta * ct;
-      if (periodic_at(rc, rc.t0 + (double)n * rc.dt)) {
-        xe = wrap_box(xe, cp.box);
-        ye = wrap_box(ye, cp.box);
-        ze = wrap_box(ze, cp.box);
-      }
-      const double ux = s.ux[gi], uy = s.uy[gi], uz = s.uz[gi];
-      s.x[ge] = xe; s.y[ge] = ye; s.z[ge] = ze;
-      s.ux[ge] = ux; s.uy[ge] = uy; s.uz[ge] = uz;
-      s.Z[ge] = -1;
-      s.wl[ge] = 0.0;
-      s.wc[ge] = 0.0;
-      s.wsp[ge] = cp.weight * gm1(ux, uy, uz);
-      const bool grid = periodic_at(rc, rc.t0 + (double)(n + 1) * rc.dt);  // records for step n + 1
-      write_source(s, PREC, grid, cp.box, ge, xe, ye, ze, -cp.kw);
-      const int znew = s.Z[gi] + 1;
-      s.Z[gi] = (int8_t)znew;
-      write_source(s, PREC, grid, cp.box, gi, s.x[gi], s.y[gi], s.z[gi], cp.kw * (double)znew);
-    }
+  const int64_t e = n_base + base + wave_off + below;
+  if (flag && e < cp.cap) spawn_electron<PREC>(s, rc, cp, c, li, e, *s.step + k);
+  if (b == cp.n_ion_blocks - 1 && threadIdx.x == 0)
+    count_spawns(s, cp, d, n_base, base + sh_wave[0] + sh_wave[1] + sh_wave[2] + sh_wave[3]);
+}
+
+// Check and spawns of a cluster in one block of NT threads, one per ion, where no cluster has more
+// ions than that: one launch instead of two, which are bound by their latency.  Blocks of 256 for any
+// number of clusters, of 1024 for at most kIonizeClusters (one per compute unit).  Back to back, 1000
+// ions take 4.4 us so and 7.5 us in two launches, 48 clusters of 1000 5.2 and 8.4, 256 of 500 4.9 and
+// 8.9; a second round of 1024 ions costs more than it saves (2000 ions: 9.1 and 8.4), and so do
+// several blocks of 1024 threads per compute unit (1000 clusters of 200: 21 and 9.4).
+constexpr int kIonizeClusters = 256;
+template <int PREC, int NT>
+__global__ __launch_bounds__(NT) void k_ionize_cluster(DevState s, RunConst rc, FieldLayout fl, int64_t k) {
+  __shared__ double sh_p[2][LC_MAX_Z];
+  __shared__ int32_t sh_wave[NT / 64];
+  const int c = blockIdx.x;
+  const ClusterParams& cp = s.cp[c];
+  ClusterDyn& d = s.dyn[c];
+  if (!d.active) return;
+  const int64_t n_base = d.n_cur, n = *s.step + k;
+  if (!rc.ofi_local) ionize_table(rc, cp, d, sh_p);
+  __syncthreads();
+  const int64_t li = threadIdx.x;
+  const int flag = li < cp.n_ion ? ion_flag(s, rc, fl, cp, d, sh_p, c, li, cp.off + li, n) : 0;
+  int count;
+  const int below = flag_rank(flag, count);
+  if ((threadIdx.x & 63) == 0) sh_wave[threadIdx.x >> 6] = count;
+  __syncthreads();  // every thread has also read n_cur
+  int before = 0, total = 0;
+#pragma unroll
+  for (int q = 0; q < NT / 64; ++q) {
+    before += q < (int)(threadIdx.x >> 6) ? sh_wave[q] : 0;
+    total += sh_wave[q];
   }
-  if (b == cp.n_ion_blocks - 1 && threadIdx.x == 0) {
-    const int64_t total = base + sh_wave[0] + sh_wave[1] + sh_wave[2] + sh_wave[3];
-    const int64_t room = cp.cap - n_base;
-    const int64_t fit = total < room ? total : room;
-    d.dropped += total - fit;
-    d.events += fit;
-    d.n_cur = n_base + fit;
-    if (total > fit) atomicOr(s.err, kFlagCapacity);
+  const int64_t e = n_base + before + below;
+  if (flag && e < cp.cap) spawn_electron<PREC>(s, rc, cp, c, li, e, n);
+  if (threadIdx.x == 0) {
+    d.n_base = n_base;
+    count_spawns(s, cp, d, n_base, total);
   }
 }
 
@@ -1038,6 +1099,17 @@ hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, c
   if (rc.collisional) {  // this step's electron density, temperature and collisional rates
     k_ci_partial<<<dim3(rc.ci_blocks, rc.n_clusters), kBlock, 0, st>>>(s, rc);
     k_ci_final<<<rc.n_clusters, 64, 0, st>>>(s, rc);
+  }
+  const int nt = rc.max_ion_blocks == 1 ? 256 : 1024;
+  if (rc.max_ion_blocks * kBlock <= nt && (nt == 256 || rc.n_clusters <= kIonizeClusters)) {
+    if (precision == LC_FP64) {
+      if (nt == 256) k_ionize_cluster<LC_FP64, 256><<<rc.n_clusters, 256, 0, st>>>(s, rc, fl, k);
+      else k_ionize_cluster<LC_FP64, 1024><<<rc.n_clusters, 1024, 0, st>>>(s, rc, fl, k);
+    } else {
+      if (nt == 256) k_ionize_cluster<LC_FP32_ACC64, 256><<<rc.n_clusters, 256, 0, st>>>(s, rc, fl, k);
+      else k_ionize_cluster<LC_FP32_ACC64, 1024><<<rc.n_clusters, 1024, 0, st>>>(s, rc, fl, k);
+    }
+    return hipGetLastError();
   }
   if (precision == LC_FP64) {
     k_ionize_check<LC_FP64><<<n_ion_blocks, kBlock, 0, st>>>(s, rc, fl, k);
