@@ -260,43 +260,44 @@ __device__ inline int wave_cluster(const DevState& s, int64_t g0) {
 }
 
 // Coulomb field of slot g from the partials of the last field pass, summed over the splits in
-// split order (FP64).  g is a global slot, or a lane's offset in a group view (group_view).
-template <typename I>
-__device__ inline void field_sum(const DevState& s, const RunConst& rc, const FieldLayout& fl, I g, double& ex,
-                                 double& ey, double& ez) {
+// split order (FP64), with PHI also the potential.  g is a global slot, or a lane's offset in a group
+// view (group_view).  The loads of BATCH splits go out together (one after the other each split waits
+// for memory); past the last split they repeat it.
+template <int BATCH, bool PHI, typename I>
+__device__ inline void split_sum(const DevState& s, const RunConst& rc, const FieldLayout& fl, I g, double* e) {
   const int64_t n = rc.n_total;
+  constexpr int NQ = PHI ? 4 : 3;
   if (fl.S == 1) {  // one split (every pair-once step): plain loads, no loop
-    ex = s.part[g];
-    ey = (s.part + n)[g];
-    ez = (s.part + 2 * n)[g];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) e[i] = (s.part + i * n)[g];
     return;
   }
-  ex = 0.0; ey = 0.0; ez = 0.0;
-  int k = 0;
-  // the loads of four splits go out together (one after the other each split waits for memory:
-  // the push of 3000 particles with 16 splits took 8.4 us, 5.4 us so)
-  for (; k + 4 <= fl.S; k += 4) {
-    double v[4][3];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double* b = s.part + (int64_t)(k + u) * kComp * n;
-      v[u][0] = b[g];
-      v[u][1] = (b + n)[g];
-      v[u][2] = (b + 2 * n)[g];
+  for (int i = 0; i < NQ; ++i) e[i] = 0.0;
+  for (int k = 0; k < fl.S; k += BATCH) {
+    double v[BATCH][NQ];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const double* b = s.part + (int64_t)min(k + u, fl.S - 1) * kComp * n;
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) v[u][i] = (b + i * n)[g];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      ex += v[u][0];
-      ey += v[u][1];
-      ez += v[u][2];
+    for (int u = 0; u < BATCH; ++u) {
+      if (k + u < fl.S) {
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) e[i] += v[u][i];
+      }
     }
   }
-  for (; k < fl.S; ++k) {
-    const double* b = s.part + (int64_t)k * kComp * n;
-    ex += b[g];
-    ey += (b + n)[g];
-    ez += (b + 2 * n)[g];
-  }
+}
+
+template <int BATCH = 4, typename I>
+__device__ inline void field_sum(const DevState& s, const RunConst& rc, const FieldLayout& fl, I g, double& ex,
+                                 double& ey, double& ez) {
+  double e[3];
+  split_sum<BATCH, false>(s, rc, fl, g, e);
+  ex = e[0]; ey = e[1]; ez = e[2];
 }
 
 // The state as seen from the 64-slot group that starts at slot g0 (wave-uniform): every

@@ -340,8 +340,8 @@ __device__ inline void push_one(const DevState& s, const RunConst& rc, uint32_t 
 // a pattern probe, two-wave groups keep every layout tried within 0.9 of the best case.
 constexpr int kPushBlock = 128;
 
-template <int PREC>
-__global__ __launch_bounds__(kPushBlock) __attribute__((amdgpu_waves_per_eu(5)))
+template <int PREC, bool MANY>
+__global__ __launch_bounds__(kPushBlock) __attribute__((amdgpu_waves_per_eu(MANY ? 2 : 5)))
 void k_push(DevState s, RunConst rc, FieldLayout fl, int64_t k, int diag) {
   const int64_t g0 = (int64_t)blockIdx.x * kPushBlock + kGroup * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (g0 >= rc.n_total) return;
@@ -355,7 +355,7 @@ void k_push(DevState s, RunConst rc, FieldLayout fl, int64_t k, int diag) {
   // together (one memory round trip instead of two)
   PState ps = load_pstate(v, rc, lane);
   double ecx, ecy, ecz;
-  field_sum(v, rc, fl, lane, ecx, ecy, ecz);
+  field_sum<MANY ? 16 : 4>(v, rc, fl, lane, ecx, ecy, ecz);
   load_seen(v, rc, lane, ps);
   push_one<PREC>(v, rc, lane, c, *s.step + k, diag, ecx, ecy, ecz, ps);
 }
@@ -501,10 +501,9 @@ __global__ __launch_bounds__(kBlock) void k_diag_partial(DevState s, RunConst rc
       const double M = (zc < 0) ? 1.0 : cp.mass_ion;
       const double w = cp.weight;
       const double ux = s.ux[g], uy = s.uy[g], uz = s.uz[g];
-      double ex, ey, ez;
-      field_sum(s, rc, fl, g, ex, ey, ez);
-      double phi = 0.0;
-      for (int k = 0; k < fl.S; ++k) phi += s.part[((int64_t)k * kComp + 3) * rc.n_total + g];
+      double e[4];
+      split_sum<8, true>(s, rc, fl, g, e);
+      const double ex = e[0], ey = e[1], ez = e[2], phi = e[3];
       q[0] += w * M * gm1(ux, uy, uz);
       q[1] += s.kebar[g];
       q[2] += 0.5 * w * (double)zc * phi;
@@ -743,7 +742,7 @@ __device__ inline int ion_flag(const DevState& s, const RunConst& rc, const Fiel
     P = table[inside ? 1 : 0][zc];
   } else {
     double ex, ey, ez;
-    field_sum(s, rc, fl, g, ex, ey, ez);
+    field_sum<8>(s, rc, fl, g, ex, ey, ez);
     ex += d.laser_e;
     ey += d.laser_ey;
     double nu = adk_nu(cp, zc, sqrt(ex * ex + ey * ey + ez * ez) * cp.field_au);
@@ -1054,8 +1053,9 @@ hipError_t launch_push(const DevState& s, const RunConst& rc, int precision, con
                        bool diag, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const dim3 pb((unsigned)((rc.n_total + kPushBlock - 1) / kPushBlock));
   const int dg = diag ? 1 : 0;
-  if (precision == LC_FP64) launch_timed(k_push<LC_FP64>, pb, dim3(kPushBlock), 0, st, e0, e1, s, rc, fl, k, dg);
-  else launch_timed(k_push<LC_FP32_ACC64>, pb, dim3(kPushBlock), 0, st, e0, e1, s, rc, fl, k, dg);
+  const auto kernel = precision == LC_FP64 ? (fl.S > 4 ? k_push<LC_FP64, true> : k_push<LC_FP64, false>)
+                                           : (fl.S > 4 ? k_push<LC_FP32_ACC64, true> : k_push<LC_FP32_ACC64, false>);
+  launch_timed(kernel, pb, dim3(kPushBlock), 0, st, e0, e1, s, rc, fl, k, dg);
   return hipGetLastError();
 }
 
