@@ -591,7 +591,7 @@ __global__ __launch_bounds__(64) void k_diag_final(DevState s, RunConst rc, int6
 // up to x = 1 (Abramowitz & Stegun 5.1.11) as a polynomial in Horner form, the continued fraction of
 // A&S 5.1.22 beyond, as the quotient of its forward recurrences (numerator and denominator are
 // brought back by a power of two every eight terms): one division instead of two per term, which
-// were most of k_ci_final's 16.2 us on the 48-cluster ensemble (9.1 us so).  The number of terms, 12 +
+// were most of k_ci_final's 16.2 us on a 48-cluster ensemble (9.1 us so).  The number of terms, 12 +
 // 84/x, covers the convergence exp(-4 (n x)^{1/2}); against long double, the relative error over
 // e^-12 < x < e^6.5 is at most 9.2e-15 (just above x = 1) and 4.9e-16 rms, with a division per term
 // 1.1e-14 and 6.1e-16.
@@ -636,27 +636,48 @@ __device__ inline double lotz_rate(double av, double q, double P, double T) {
 
 // Electron count and kinetic energy (sum of gamma - 1) inside the sphere of radius R0 about
 // the cluster centre: rc.ci_blocks blocks per cluster (sized by the largest capacity, at most
-// kDiagBlocks) over its electron slots, fixed-order reductions (as the diagnostics).
-__global__ __launch_bounds__(kBlock) void k_ci_partial(DevState s, RunConst rc) {
-  __shared__ double sh[4][2];
-  const int c = blockIdx.y;
-  const ClusterParams& cp = s.cp[c];
-  const ClusterDyn& d = s.dyn[c];
-  double cnt = 0.0, ke = 0.0;
+// kDiagBlocks) of 256 threads over its electron slots, fixed-order reductions (as the diagnostics).
+// ci_wave_sums adds up a wave's share (its partial sums in every lane): thread t of block b takes
+// every (256 ci_blocks)-th slot, U of them at a time, their loads together; with U = 1 momenta are
+// loaded inside the sphere only (many blocks, bound by memory: four at a time took 15.0 instead of
+// 11.4 us for 400 clusters of 5200).
+template <int U>
+__device__ inline void ci_wave_sums(const DevState& s, const RunConst& rc, const ClusterParams& cp,
+                                    const ClusterDyn& d, int b, int t, double& cnt, double& ke) {
+  cnt = 0.0; ke = 0.0;
   if (d.active) {
-    for (int64_t li = cp.n_ion + (int64_t)blockIdx.x * kBlock + threadIdx.x; li < d.n_cur;
-         li += (int64_t)rc.ci_blocks * kBlock) {
-      const int64_t g = cp.off + li;
-      const double x = s.x[g], y = s.y[g], z = s.z[g];
-      if (x * x + y * y + z * z < cp.ci_r2) {
-        cnt += 1.0;
-        ke += gm1(s.ux[g], s.uy[g], s.uz[g]);
+    const int64_t stride = (int64_t)rc.ci_blocks * kBlock, n_cur = d.n_cur;
+    for (int64_t base = cp.n_ion + (int64_t)b * kBlock + t; base < n_cur; base += U * stride) {
+      double r2[U], u[U][3];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        if (base + i * stride < n_cur) {
+          const int64_t g = cp.off + base + i * stride;
+          const double x = s.x[g], y = s.y[g], z = s.z[g];
+          if (U > 1) { u[i][0] = s.ux[g]; u[i][1] = s.uy[g]; u[i][2] = s.uz[g]; }
+          r2[i] = x * x + y * y + z * z;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        if (base + i * stride < n_cur && r2[i] < cp.ci_r2) {
+          const int64_t g = cp.off + base + i * stride;
+          cnt += 1.0;
+          ke += U > 1 ? gm1(u[i][0], u[i][1], u[i][2]) : gm1(s.ux[g], s.uy[g], s.uz[g]);
+        }
       }
     }
   }
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const double a = wave_sum(cnt), b = wave_sum(ke);
-  if (lane == 0) { sh[wv][0] = a; sh[wv][1] = b; }
+  cnt = wave_sum(cnt);
+  ke = wave_sum(ke);
+}
+
+__global__ __launch_bounds__(kBlock) void k_ci_partial(DevState s, RunConst rc) {
+  __shared__ double sh[4][2];
+  const int c = blockIdx.y;
+  double a, b;
+  ci_wave_sums<1>(s, rc, s.cp[c], s.dyn[c], blockIdx.x, threadIdx.x, a, b);
+  if ((threadIdx.x & 63) == 0) { sh[threadIdx.x >> 6][0] = a; sh[threadIdx.x >> 6][1] = b; }
   __syncthreads();
   if (threadIdx.x < 2) {
     const int i = threadIdx.x;
@@ -664,33 +685,34 @@ __global__ __launch_bounds__(kBlock) void k_ci_partial(DevState s, RunConst rc) 
   }
 }
 
-// n_e (cm^-3) and T = (2/3) <KE> (eV) from the partials in block order, then the rate of every
-// charge state in units of 1/w.
-__global__ __launch_bounds__(64) void k_ci_final(DevState s, RunConst rc) {
-  __shared__ double sh_ne, sh_te;
+// n_e (cm^-3) and T = (2/3) <KE> (eV) from the partials part(b, 0 or 1) of blocks b in block order,
+// and the rate of charge state z in units of 1/w.
+template <typename P>
+__device__ inline double ci_rate(const RunConst& rc, const ClusterParams& cp, int z, P part) {
+  double cnt = 0.0, ke = 0.0;
+  for (int b = 0; b < rc.ci_blocks; ++b) {
+    cnt += part(b, 0);
+    ke += part(b, 1);
+  }
+  const double ne = cnt * cp.ne_per_macro;
+  const double te = (cnt > 0.0) ? (2.0 / 3.0) * (ke / cnt) * rc.mec2_ev : 0.0;
+  return ne * lotz_rate(cp.lotz_av, cp.lotz_q[z], cp.ci_ip_ev[z], te) * cp.s_per_unit;
+}
+
+// Rates of every charge state of cluster c from k_ci_partial's sums, in nu[] of the block (a barrier
+// follows before their use): the partials load in parallel, and a lane per charge state adds them up.
+__device__ inline void ci_rates(const DevState& s, const RunConst& rc, const ClusterParams& cp, int c,
+                                double (*sh_part)[2], double* nu) {
+  const int t = threadIdx.x;
+  if (t < 2 * rc.ci_blocks) sh_part[t >> 1][t & 1] = s.ci_part[(int64_t)c * kDiagBlocks * 2 + t];
+  __syncthreads();
+  if (t < LC_MAX_Z) nu[t] = ci_rate(rc, cp, t, [&](int b, int i) { return sh_part[b][i]; });
+}
+
+__global__ __launch_bounds__(2 * kDiagBlocks) void k_ci_final(DevState s, RunConst rc) {
   __shared__ double sh_part[kDiagBlocks][2];
   const int c = blockIdx.x;
-  const ClusterParams& cp = s.cp[c];
-  ClusterDyn& d = s.dyn[c];
-  if (threadIdx.x < rc.ci_blocks) {  // the partials load in parallel, then add in block order
-    sh_part[threadIdx.x][0] = s.ci_part[((int64_t)c * kDiagBlocks + threadIdx.x) * 2];
-    sh_part[threadIdx.x][1] = s.ci_part[((int64_t)c * kDiagBlocks + threadIdx.x) * 2 + 1];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double cnt = 0.0, ke = 0.0;
-    for (int b = 0; b < rc.ci_blocks; ++b) {
-      cnt += sh_part[b][0];
-      ke += sh_part[b][1];
-    }
-    sh_ne = cnt * cp.ne_per_macro;
-    sh_te = (cnt > 0.0) ? (2.0 / 3.0) * (ke / cnt) * rc.mec2_ev : 0.0;
-  }
-  __syncthreads();
-  if (threadIdx.x < LC_MAX_Z) {
-    const int z = threadIdx.x;
-    d.ci_nu[z] = sh_ne * lotz_rate(cp.lotz_av, cp.lotz_q[z], cp.ci_ip_ev[z], sh_te) * cp.s_per_unit;
-  }
+  ci_rates(s, rc, s.cp[c], c, sh_part, s.dyn[c].ci_nu);
 }
 
 // ----------------------------------------------------------------------------- ionization (S4)
@@ -711,13 +733,13 @@ __device__ inline double laser_strength(const ClusterParams& cp, const ClusterDy
 // so threads 0 .. 31 of a block evaluate P = 1 - exp(-nu dt) for every state once, with the same
 // arithmetic as ion_flag for LC_LOCAL.
 __device__ inline void ionize_table(const RunConst& rc, const ClusterParams& cp, const ClusterDyn& d,
-                                    double (*p)[LC_MAX_Z]) {
+                                    const double* ci_nu, double (*p)[LC_MAX_Z]) {
   if (threadIdx.x < 2 * LC_MAX_Z) {
     const int z = threadIdx.x % LC_MAX_Z, inside = threadIdx.x / LC_MAX_Z;
     double P = 0.0;
     if (z < cp.z_max && cp.adk_ok[z]) {
       double nu = adk_nu(cp, z, laser_strength(cp, d) * cp.field_au);
-      if (inside) nu += d.ci_nu[z];
+      if (inside) nu += ci_nu[z];
       P = -expm1(-nu * rc.dt);
     }
     p[inside][z] = P;
@@ -728,8 +750,8 @@ __device__ inline void ionize_table(const RunConst& rc, const ClusterParams& cp,
 // P = 1 - exp(-nu dt), nu the ADK rate at the driving field (plus the collisional rate inside the
 // cluster sphere).  An ion whose P is exactly 0 cannot ionize (alpha > 0) and takes no draw.
 __device__ inline int ion_flag(const DevState& s, const RunConst& rc, const FieldLayout& fl, const ClusterParams& cp,
-                               const ClusterDyn& d, const double (*table)[LC_MAX_Z], int c, int64_t li, int64_t g,
-                               int64_t n) {
+                               const ClusterDyn& d, const double* ci_nu, const double (*table)[LC_MAX_Z], int c,
+                               int64_t li, int64_t g, int64_t n) {
   const int zc = s.Z[g];
   if (!(zc >= 0 && zc < cp.z_max && cp.adk_ok[zc])) return 0;
   bool inside = false;
@@ -742,11 +764,11 @@ __device__ inline int ion_flag(const DevState& s, const RunConst& rc, const Fiel
     P = table[inside ? 1 : 0][zc];
   } else {
     double ex, ey, ez;
-    field_sum<8>(s, rc, fl, g, ex, ey, ez);
+    field_sum(s, rc, fl, g, ex, ey, ez);
     ex += d.laser_e;
     ey += d.laser_ey;
     double nu = adk_nu(cp, zc, sqrt(ex * ex + ey * ey + ez * ez) * cp.field_au);
-    if (inside) nu += d.ci_nu[zc];
+    if (inside) nu += ci_nu[zc];
     P = -expm1(-nu * rc.dt);
   }
   if (!(P > 0.0)) return 0;
@@ -754,10 +776,15 @@ __device__ inline int ion_flag(const DevState& s, const RunConst& rc, const Fiel
   return (unit_interval(r.v[0]) < P) ? 1 : 0;
 }
 
-// Flags of a block's 256 ions, and their count.
+// Flags of a block's 256 ions, and their count.  With own_rates every block forms its cluster's
+// collisional rates from the partials (the first one keeps them), else k_ci_final has: up to 2048
+// blocks that costs less than a launch (check, spawns and rates of 48 clusters of 5000 ions: 15.2
+// against 17.4 us, of 100 of 2600 15.7 and 17.7; of 400 of 2600, 4400 blocks, 39.9 and 40.2).
+constexpr int kOwnRates = 2048;
 template <int PREC>
-__global__ __launch_bounds__(kBlock) void k_ionize_check(DevState s, RunConst rc, FieldLayout fl, int64_t k) {
-  __shared__ double sh_p[2][LC_MAX_Z];
+__global__ __launch_bounds__(kBlock) void k_ionize_check(DevState s, RunConst rc, FieldLayout fl, int64_t k,
+                                                         int own_rates) {
+  __shared__ double sh_p[2][LC_MAX_Z], sh_nu[LC_MAX_Z], sh_part[kDiagBlocks][2];
   const int ibk = blockIdx.x;
   const int c = s.ib_cluster[ibk];
   const ClusterParams& cp = s.cp[c];
@@ -765,14 +792,21 @@ __global__ __launch_bounds__(kBlock) void k_ionize_check(DevState s, RunConst rc
   const int b = ibk - cp.ion_block0;
   const int64_t li = (int64_t)b * kBlock + threadIdx.x;
   if (b == 0 && threadIdx.x == 0) d.n_base = d.n_cur;
+  const double* ci_nu = d.ci_nu;
+  if (own_rates) {
+    ci_rates(s, rc, cp, c, sh_part, sh_nu);
+    ci_nu = sh_nu;
+    __syncthreads();
+    if (b == 0 && threadIdx.x < LC_MAX_Z) d.ci_nu[threadIdx.x] = sh_nu[threadIdx.x];
+  }
   if (!rc.ofi_local) {  // uniform over the launch
-    ionize_table(rc, cp, d, sh_p);
+    ionize_table(rc, cp, d, ci_nu, sh_p);
     __syncthreads();
   }
   int flag = 0;
   if (d.active && li < cp.n_ion) {
     const int64_t g = cp.off + li;
-    flag = ion_flag(s, rc, fl, cp, d, sh_p, c, li, g, *s.step + k);
+    flag = ion_flag(s, rc, fl, cp, d, ci_nu, sh_p, c, li, g, *s.step + k);
     s.flag[g] = flag;
   }
   const int cnt = __syncthreads_count(flag);
@@ -929,21 +963,41 @@ __global__ __launch_bounds__(kBlock) void k_ionize_spawn(DevState s, RunConst rc
 // number of clusters, of 1024 for at most kIonizeClusters (one per compute unit).  Back to back, 1000
 // ions take 4.4 us so and 7.5 us in two launches, 48 clusters of 1000 5.2 and 8.4, 256 of 500 4.9 and
 // 8.9; a second round of 1024 ions costs more than it saves (2000 ions: 9.1 and 8.4), and so do
-// several blocks of 1024 threads per compute unit (1000 clusters of 200: 21 and 9.4).
+// several blocks of 1024 threads per compute unit (1000 clusters of 200: 21 and 9.4).  Collisional
+// rates are formed here too, from the block's own sums where it holds the threads of every block of
+// k_ci_partial, with the same sums: 250 ions 7.5 us and 12.4 in four launches, 1000 9.1 and 12.8, 900
+// clusters of 200 8.0 and 15.9.
 constexpr int kIonizeClusters = 256;
 template <int PREC, int NT>
 __global__ __launch_bounds__(NT) void k_ionize_cluster(DevState s, RunConst rc, FieldLayout fl, int64_t k) {
-  __shared__ double sh_p[2][LC_MAX_Z];
+  __shared__ double sh_p[2][LC_MAX_Z], sh_nu[LC_MAX_Z], sh_part[kDiagBlocks][2];
   __shared__ int32_t sh_wave[NT / 64];
   const int c = blockIdx.x;
   const ClusterParams& cp = s.cp[c];
   ClusterDyn& d = s.dyn[c];
   if (!d.active) return;
   const int64_t n_base = d.n_cur, n = *s.step + k;
-  if (!rc.ofi_local) ionize_table(rc, cp, d, sh_p);
+  if (rc.collisional) {
+    if (rc.ci_blocks <= NT / kBlock) {  // the sums in this block too, of its 256-thread parts
+      const int b = threadIdx.x / kBlock, w = threadIdx.x >> 6;
+      double cnt = 0.0, ke = 0.0;
+      if (b < rc.ci_blocks) ci_wave_sums<4>(s, rc, cp, d, b, threadIdx.x % kBlock, cnt, ke);
+      if ((threadIdx.x & 63) == 0) { sh_part[w][0] = cnt; sh_part[w][1] = ke; }
+      __syncthreads();
+      if (threadIdx.x < LC_MAX_Z)
+        sh_nu[threadIdx.x] = ci_rate(rc, cp, threadIdx.x, [&](int q, int i) {
+          return ((sh_part[4 * q][i] + sh_part[4 * q + 1][i]) + sh_part[4 * q + 2][i]) + sh_part[4 * q + 3][i];
+        });
+    } else {
+      ci_rates(s, rc, cp, c, sh_part, sh_nu);
+    }
+    __syncthreads();
+    if (threadIdx.x < LC_MAX_Z) d.ci_nu[threadIdx.x] = sh_nu[threadIdx.x];
+  }
+  if (!rc.ofi_local) ionize_table(rc, cp, d, sh_nu, sh_p);
   __syncthreads();
   const int64_t li = threadIdx.x;
-  const int flag = li < cp.n_ion ? ion_flag(s, rc, fl, cp, d, sh_p, c, li, cp.off + li, n) : 0;
+  const int flag = li < cp.n_ion ? ion_flag(s, rc, fl, cp, d, sh_nu, sh_p, c, li, cp.off + li, n) : 0;
   int count;
   const int below = flag_rank(flag, count);
   if ((threadIdx.x & 63) == 0) sh_wave[threadIdx.x >> 6] = count;
@@ -1096,12 +1150,15 @@ hipError_t launch_diag(const DevState& s, const RunConst& rc, const FieldLayout&
 hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, const FieldLayout& fl, int64_t k,
                          int n_ion_blocks, hipStream_t st) {
   if (n_ion_blocks <= 0) return hipSuccess;
-  if (rc.collisional) {  // this step's electron density, temperature and collisional rates
-    k_ci_partial<<<dim3(rc.ci_blocks, rc.n_clusters), kBlock, 0, st>>>(s, rc);
-    k_ci_final<<<rc.n_clusters, 64, 0, st>>>(s, rc);
-  }
   const int nt = rc.max_ion_blocks == 1 ? 256 : 1024;
-  if (rc.max_ion_blocks * kBlock <= nt && (nt == 256 || rc.n_clusters <= kIonizeClusters)) {
+  const bool one_block = rc.max_ion_blocks * kBlock <= nt && (nt == 256 || rc.n_clusters <= kIonizeClusters);
+  const int own_rates = rc.collisional && n_ion_blocks <= kOwnRates ? 1 : 0;
+  if (rc.collisional) {  // this step's electron density, temperature and collisional rates
+    if (!one_block || rc.ci_blocks > nt / kBlock)
+      k_ci_partial<<<dim3(rc.ci_blocks, rc.n_clusters), kBlock, 0, st>>>(s, rc);
+    if (!one_block && !own_rates) k_ci_final<<<rc.n_clusters, 2 * kDiagBlocks, 0, st>>>(s, rc);
+  }
+  if (one_block) {
     if (precision == LC_FP64) {
       if (nt == 256) k_ionize_cluster<LC_FP64, 256><<<rc.n_clusters, 256, 0, st>>>(s, rc, fl, k);
       else k_ionize_cluster<LC_FP64, 1024><<<rc.n_clusters, 1024, 0, st>>>(s, rc, fl, k);
@@ -1112,9 +1169,9 @@ hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, c
     return hipGetLastError();
   }
   if (precision == LC_FP64) {
-    k_ionize_check<LC_FP64><<<n_ion_blocks, kBlock, 0, st>>>(s, rc, fl, k);
+    k_ionize_check<LC_FP64><<<n_ion_blocks, kBlock, 0, st>>>(s, rc, fl, k, own_rates);
   } else {
-    k_ionize_check<LC_FP32_ACC64><<<n_ion_blocks, kBlock, 0, st>>>(s, rc, fl, k);
+    k_ionize_check<LC_FP32_ACC64><<<n_ion_blocks, kBlock, 0, st>>>(s, rc, fl, k, own_rates);
   }
   const int scanned = rc.max_ion_blocks > kSpawnDirect ? 1 : 0;
   if (scanned) k_ionize_scan<<<1, 1024, 0, st>>>(s, n_ion_blocks);
