@@ -481,11 +481,14 @@ hipError_t enqueue_steps(lc_sim* s, int count, int64_t first_step) {
       e = launch_diag(s->s, s->rc, fl, 0, s->stream);
       if (e != hipSuccess) return e;
     }
+    const bool n3_next = n3_pass(s, ft, is_diag_step(s, first_step + k + 1));
+    const bool closes = s->cfg.ionize && ionize_schedules(s->rc);
     if (s->cfg.ionize) {
-      e = launch_ionize(s->s, s->rc, s->cfg.precision, fl, 0, s->L.n_ion_blocks, s->stream);
+      const ForceTiling next = pass_tiling(s, ft, n3_next);
+      e = launch_ionize(s->s, s->rc, s->cfg.precision, fl, 0, s->L.n_ion_blocks, s->stream, closes ? &next : nullptr,
+                        n3_next);
       if (e != hipSuccess) return e;
     }
-    const bool n3_next = n3_pass(s, ft, is_diag_step(s, first_step + k + 1));
     // Without ionization no particle count changes, so between two steps of this group that
     // take the same kind of pass (pair-once, or one-sided) the tile tables stay as they are:
     // the schedule is left out and the next step's force launch does its bookkeeping (step
@@ -495,7 +498,7 @@ hipError_t enqueue_steps(lc_sim* s, int count, int64_t first_step) {
     // always schedules, so the device state between calls is the same as with a schedule
     // after every step.
     begin = tab && n3 == n3_next && !pass_tiling(s, ft, n3).persistent && k + 1 < tab_steps;
-    if (!begin) {
+    if (!begin && !closes) {
       e = schedule(s, ft, n3_next, true);
       if (e != hipSuccess) return e;
     }

@@ -428,7 +428,11 @@ hipError_t launch_start_kick(const DevState& s, const RunConst& rc, int precisio
                              hipStream_t st);
 hipError_t launch_diag(const DevState& s, const RunConst& rc, const FieldLayout& fl, int64_t k, hipStream_t st);
 hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, const FieldLayout& fl, int64_t k,
-                         int n_ion_blocks, hipStream_t st);
+                         int n_ion_blocks, hipStream_t st, const ForceTiling* next = nullptr,
+                         bool n3_next = false);
+// Whether launch_ionize closes the step: given the next pass's tiling, it also does the work of
+// launch_schedule with advance = true.
+bool ionize_schedules(const RunConst& rc);
 // Initial placement of cluster c on the device (Sec. II random atoms inside R0): n_ion ions,
 // each with z_init electrons, and the cluster's live count n_ion (1 + z_init).
 hipError_t launch_init_generate(const DevState& s, const RunConst& rc, int c, int64_t n_ion, int z_init,

@@ -149,9 +149,9 @@ __global__ __launch_bounds__(kBlock) void k_laser_table(DevState s, RunConst rc,
   row[2] = ey;
 }
 
-// Up to 64 clusters: one wave, the scan across its lanes without barriers.
-__global__ __launch_bounds__(64) void k_schedule_wave(DevState s, RunConst rc, int TI, int S, int n3, int advance) {
-  const int p = threadIdx.x;
+// Up to 64 clusters: one wave (p its lane), the scan across its lanes without barriers.
+__device__ inline void schedule_wave(const DevState& s, const RunConst& rc, int p, int TI, int S, int n3,
+                                     int advance) {
   const int64_t n = *s.step + advance;
   const double t = rc.t0 + (double)n * rc.dt;
   const int32_t tiles = (p < rc.n_clusters) ? schedule_cluster(s, p, TI, S, n3, advance, n, t) : 0;
@@ -170,6 +170,10 @@ __global__ __launch_bounds__(64) void k_schedule_wave(DevState s, RunConst rc, i
     *s.queue = 0;
     if (advance) *s.step = n;  // every lane read the old index at the start
   }
+}
+
+__global__ __launch_bounds__(64) void k_schedule_wave(DevState s, RunConst rc, int TI, int S, int n3, int advance) {
+  schedule_wave(s, rc, threadIdx.x, TI, S, n3, advance);
 }
 
 __global__ __launch_bounds__(kBlock) void k_schedule(DevState s, RunConst rc, int TI, int S, int n3,
@@ -966,54 +970,63 @@ __global__ __launch_bounds__(kBlock) void k_ionize_spawn(DevState s, RunConst rc
 // several blocks of 1024 threads per compute unit (1000 clusters of 200: 21 and 9.4).  Collisional
 // rates are formed here too, from the block's own sums where it holds the threads of every block of
 // k_ci_partial, with the same sums: 250 ions 7.5 us and 12.4 in four launches, 1000 9.1 and 12.8, 900
-// clusters of 200 8.0 and 15.9.
+// clusters of 200 8.0 and 15.9.  With a single cluster the block also closes the step (TI > 0, else
+// launch_schedule does): a launch less of the four or five that a small run takes per step, 100
+// steps of one of 720 macroparticles 1.67 -> 1.59 ms.  For several clusters the last block to end
+// would have to do it, and what it waits for the others' counts costs what the launch does (36
+// clusters: 4.41 against 4.44 ms).
 constexpr int kIonizeClusters = 256;
 template <int PREC, int NT>
-__global__ __launch_bounds__(NT) void k_ionize_cluster(DevState s, RunConst rc, FieldLayout fl, int64_t k) {
+__global__ __launch_bounds__(NT) void k_ionize_cluster(DevState s, RunConst rc, FieldLayout fl, int64_t k, int TI,
+                                                       int S, int n3) {
   __shared__ double sh_p[2][LC_MAX_Z], sh_nu[LC_MAX_Z], sh_part[kDiagBlocks][2];
   __shared__ int32_t sh_wave[NT / 64];
   const int c = blockIdx.x;
   const ClusterParams& cp = s.cp[c];
   ClusterDyn& d = s.dyn[c];
-  if (!d.active) return;
-  const int64_t n_base = d.n_cur, n = *s.step + k;
-  if (rc.collisional) {
-    if (rc.ci_blocks <= NT / kBlock) {  // the sums in this block too, of its 256-thread parts
-      const int b = threadIdx.x / kBlock, w = threadIdx.x >> 6;
-      double cnt = 0.0, ke = 0.0;
-      if (b < rc.ci_blocks) ci_wave_sums<4>(s, rc, cp, d, b, threadIdx.x % kBlock, cnt, ke);
-      if ((threadIdx.x & 63) == 0) { sh_part[w][0] = cnt; sh_part[w][1] = ke; }
+  if (d.active) {
+    const int64_t n_base = d.n_cur, n = *s.step + k;
+    if (rc.collisional) {
+      if (rc.ci_blocks <= NT / kBlock) {  // the sums in this block too, of its 256-thread parts
+        const int b = threadIdx.x / kBlock, w = threadIdx.x >> 6;
+        double cnt = 0.0, ke = 0.0;
+        if (b < rc.ci_blocks) ci_wave_sums<4>(s, rc, cp, d, b, threadIdx.x % kBlock, cnt, ke);
+        if ((threadIdx.x & 63) == 0) { sh_part[w][0] = cnt; sh_part[w][1] = ke; }
+        __syncthreads();
+        if (threadIdx.x < LC_MAX_Z)
+          sh_nu[threadIdx.x] = ci_rate(rc, cp, threadIdx.x, [&](int q, int i) {
+            return ((sh_part[4 * q][i] + sh_part[4 * q + 1][i]) + sh_part[4 * q + 2][i]) + sh_part[4 * q + 3][i];
+          });
+      } else {
+        ci_rates(s, rc, cp, c, sh_part, sh_nu);
+      }
       __syncthreads();
-      if (threadIdx.x < LC_MAX_Z)
-        sh_nu[threadIdx.x] = ci_rate(rc, cp, threadIdx.x, [&](int q, int i) {
-          return ((sh_part[4 * q][i] + sh_part[4 * q + 1][i]) + sh_part[4 * q + 2][i]) + sh_part[4 * q + 3][i];
-        });
-    } else {
-      ci_rates(s, rc, cp, c, sh_part, sh_nu);
+      if (threadIdx.x < LC_MAX_Z) d.ci_nu[threadIdx.x] = sh_nu[threadIdx.x];
     }
+    if (!rc.ofi_local) ionize_table(rc, cp, d, sh_nu, sh_p);
     __syncthreads();
-    if (threadIdx.x < LC_MAX_Z) d.ci_nu[threadIdx.x] = sh_nu[threadIdx.x];
-  }
-  if (!rc.ofi_local) ionize_table(rc, cp, d, sh_nu, sh_p);
-  __syncthreads();
-  const int64_t li = threadIdx.x;
-  const int flag = li < cp.n_ion ? ion_flag(s, rc, fl, cp, d, sh_nu, sh_p, c, li, cp.off + li, n) : 0;
-  int count;
-  const int below = flag_rank(flag, count);
-  if ((threadIdx.x & 63) == 0) sh_wave[threadIdx.x >> 6] = count;
-  __syncthreads();  // every thread has also read n_cur
-  int before = 0, total = 0;
+    const int64_t li = threadIdx.x;
+    const int flag = li < cp.n_ion ? ion_flag(s, rc, fl, cp, d, sh_nu, sh_p, c, li, cp.off + li, n) : 0;
+    int count;
+    const int below = flag_rank(flag, count);
+    if ((threadIdx.x & 63) == 0) sh_wave[threadIdx.x >> 6] = count;
+    __syncthreads();  // every thread has also read n_cur
+    int before = 0, total = 0;
 #pragma unroll
-  for (int q = 0; q < NT / 64; ++q) {
-    before += q < (int)(threadIdx.x >> 6) ? sh_wave[q] : 0;
-    total += sh_wave[q];
+    for (int q = 0; q < NT / 64; ++q) {
+      before += q < (int)(threadIdx.x >> 6) ? sh_wave[q] : 0;
+      total += sh_wave[q];
+    }
+    const int64_t e = n_base + before + below;
+    if (flag && e < cp.cap) spawn_electron<PREC>(s, rc, cp, c, li, e, n);
+    if (threadIdx.x == 0) {
+      d.n_base = n_base;
+      count_spawns(s, cp, d, n_base, total);
+    }
   }
-  const int64_t e = n_base + before + below;
-  if (flag && e < cp.cap) spawn_electron<PREC>(s, rc, cp, c, li, e, n);
-  if (threadIdx.x == 0) {
-    d.n_base = n_base;
-    count_spawns(s, cp, d, n_base, total);
-  }
+  if (TI == 0) return;
+  __syncthreads();  // every thread has read the step index and the cluster's state
+  if (threadIdx.x < 64) schedule_wave(s, rc, threadIdx.x, TI, S, n3, 1);
 }
 
 // ----------------------------------------------------------------------------- initial placement
@@ -1147,11 +1160,21 @@ hipError_t launch_diag(const DevState& s, const RunConst& rc, const FieldLayout&
   return hipGetLastError();
 }
 
+// Threads of the one block that ionizes a cluster, 0 where k_ionize_check and k_ionize_spawn do.
+int ionize_threads(const RunConst& rc) {
+  if (rc.max_ion_blocks == 1) return 256;
+  return rc.max_ion_blocks * kBlock <= 1024 && rc.n_clusters <= kIonizeClusters ? 1024 : 0;
+}
+
+bool ionize_schedules(const RunConst& rc) {
+  return rc.max_ion_blocks > 0 && ionize_threads(rc) > 0 && rc.n_clusters == 1;
+}
+
 hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, const FieldLayout& fl, int64_t k,
-                         int n_ion_blocks, hipStream_t st) {
+                         int n_ion_blocks, hipStream_t st, const ForceTiling* next, bool n3_next) {
   if (n_ion_blocks <= 0) return hipSuccess;
-  const int nt = rc.max_ion_blocks == 1 ? 256 : 1024;
-  const bool one_block = rc.max_ion_blocks * kBlock <= nt && (nt == 256 || rc.n_clusters <= kIonizeClusters);
+  const int nt = ionize_threads(rc);
+  const bool one_block = nt > 0;
   const int own_rates = rc.collisional && n_ion_blocks <= kOwnRates ? 1 : 0;
   if (rc.collisional) {  // this step's electron density, temperature and collisional rates
     if (!one_block || rc.ci_blocks > nt / kBlock)
@@ -1159,13 +1182,11 @@ hipError_t launch_ionize(const DevState& s, const RunConst& rc, int precision, c
     if (!one_block && !own_rates) k_ci_final<<<rc.n_clusters, 2 * kDiagBlocks, 0, st>>>(s, rc);
   }
   if (one_block) {
-    if (precision == LC_FP64) {
-      if (nt == 256) k_ionize_cluster<LC_FP64, 256><<<rc.n_clusters, 256, 0, st>>>(s, rc, fl, k);
-      else k_ionize_cluster<LC_FP64, 1024><<<rc.n_clusters, 1024, 0, st>>>(s, rc, fl, k);
-    } else {
-      if (nt == 256) k_ionize_cluster<LC_FP32_ACC64, 256><<<rc.n_clusters, 256, 0, st>>>(s, rc, fl, k);
-      else k_ionize_cluster<LC_FP32_ACC64, 1024><<<rc.n_clusters, 1024, 0, st>>>(s, rc, fl, k);
-    }
+    const int TI = !next ? 0 : n3_next ? n3_block_size(*next) : force_tile_targets(*next), S = next ? next->S : 0;
+    const auto kernel =
+        precision == LC_FP64 ? (nt == 256 ? k_ionize_cluster<LC_FP64, 256> : k_ionize_cluster<LC_FP64, 1024>)
+                             : (nt == 256 ? k_ionize_cluster<LC_FP32_ACC64, 256> : k_ionize_cluster<LC_FP32_ACC64, 1024>);
+    kernel<<<rc.n_clusters, nt, 0, st>>>(s, rc, fl, k, TI, S, n3_next ? 1 : 0);
     return hipGetLastError();
   }
   if (precision == LC_FP64) {
