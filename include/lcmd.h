@@ -345,7 +345,7 @@ void lc_destroy(lc_sim* sim);
 /* Workspace bytes for lc_field with n particles, a precision and a tiling (NULL: default);
  * 0 for an invalid precision, tiling or n < 0.  One-sided tilings need S * 32 bytes per
  * particle plus the source records; that is always enough for the default too, which asks for
- * more (up to LC_FIELD_STATIC_MAX_BYTES) from 3584 particles on, to evaluate each pair once.  A
+ * more (up to LC_FIELD_STATIC_MAX_BYTES) past 4096 particles, to evaluate each pair once.  A
  * pair-once tiling (newton3 = 1, blocks of B slots) keeps 3 n ceil(n / B) partial sums in the
  * pair type, about 12 n^2 / B bytes in FP32 (47 GB at n = 1M, B = 256) and twice that in FP64. */
 size_t lc_field_workspace_bytes(int32_t precision, int64_t n, const lc_tuning* t);

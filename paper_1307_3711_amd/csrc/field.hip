@@ -11,31 +11,28 @@
 namespace lc {
 namespace {
 
-// One launch, straight from the caller's arrays to the caller's results.  A block takes 16 R
-// targets and all sources, which it stages kChunk at a time in LDS in the pair type; the 64 lanes
-// of a wave are 16 target columns (R targets each) x 4 sources, so the block's 16 waves meet 64
-// sources at a time and a small n still fills the chip.  The 64 partial sums of a target are added
-// in a fixed order; sums run in the pair type over a lane's sources of one chunk (32), in FP64
-// beyond.
+// One launch, straight from the caller's arrays to the caller's results.  A block of WAVES waves takes
+// COLS targets and all sources, which it stages kChunk at a time in LDS in the pair type; the 64 lanes
+// of a wave are COLS targets x 64 / COLS sources, so a block of 16 targets and 16 waves meets 64 sources
+// at a time and a small n still fills the chip.  The partial sums of a target are added in a fixed
+// order; sums run in the pair type over a lane's sources of one chunk (32, or 64 with 8 waves and 16
+// targets), in FP64 beyond.  Only the step of sources that holds the block's own targets tests for
+// them.
 // Bound by launch and load latency below a few thousand charges, by VALU issue beyond.  Measured a
-// call (field and potential): 1000 charges in FP64 13 us, 4099 with Kahan sums 28 us, against 120
+// call (field and potential): 1000 charges in FP64 12 us, 4099 with Kahan sums 21 us, against 120
 // and 902 us with the one-sided tiling of force.hip that a default call took before (blocks of 512
 // or 1024 targets: 2 and 5 of them on 256 compute units).  Two and four targets per lane were
 // slower at every size from 4000 charges on (20,000 FP32: 222 and 243 us against 174 us): one
 // block of 16 waves per compute unit instead of two waits at every chunk's barriers.
-constexpr int kCols = 16;              // target columns of a block
-constexpr int kGroups = 64 / kCols;    // sources a wave meets at a time
-constexpr int kWaves = 16;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kStep = kGroups * kWaves;  // sources the block meets at a time
 constexpr int kChunk = 2048;
+constexpr int64_t kUnits = 256;     // compute units
 constexpr int64_t kGrid = 1 << 20;  // blocks of a launch at most (they stride over the targets)
 
-// The lane's targets and their sums over a chunk (c: Kahan compensations).
-template <typename T, int R>
+// The lane's target and its sums over a chunk (c: Kahan compensations).
+template <typename T>
 struct Lane {
-  T x[R], y[R], z[R];
-  T f[R][4], c[R][4];
+  T x, y, z;
+  T f[4], c[4];
 };
 
 template <typename T, bool KAHAN>
@@ -49,84 +46,83 @@ __device__ inline void add_term(T a, T b, T& f, T& c) {  // f += a b
   }
 }
 
-// One source against the lane's targets.  UNIFORM: the charge is left to the caller.  MASK: the
-// source counts only if live, and not in the potential of target r when self == 16 r.
-template <typename T, int R, bool KAHAN, bool PHI, bool UNIFORM, bool MASK, typename V4>
-__device__ inline void direct_pair(const V4 s, bool live, int64_t self, T eps2, Lane<T, R>& l) {
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const T dx = l.x[r] - s.x, dy = l.y[r] - s.y, dz = l.z[r] - s.z;
-    T r2 = n3_fma(dx, dx, eps2);
-    r2 = n3_fma(dy, dy, r2);
-    r2 = n3_fma(dz, dz, r2);
-    T qinv = 0, sc;
-    if (PHI || sizeof(T) == 4) {
-      T inv = n3_rsq(r2);
-      if (MASK && !live) inv = 0;
-      qinv = UNIFORM ? inv : s.w * inv;
-      sc = qinv * (inv * inv);
-    } else {
-      sc = n3_cubed(r2);
-      if (MASK && !live) sc = 0;
-      if (!UNIFORM) sc *= s.w;
-    }
-    add_term<T, KAHAN>(sc, dx, l.f[r][0], l.c[r][0]);
-    add_term<T, KAHAN>(sc, dy, l.f[r][1], l.c[r][1]);
-    add_term<T, KAHAN>(sc, dz, l.f[r][2], l.c[r][2]);
-    if (PHI) {
-      if (MASK && self == kCols * r) qinv = 0;
-      if (KAHAN) add_term<T, true>(qinv, T(1), l.f[r][3], l.c[r][3]);
-      else l.f[r][3] += qinv;
-    }
+// One source against the lane's target.  UNIFORM: the charge is left to the caller.  MASK: the
+// source counts only if live, and in the potential only if not the target itself.
+template <typename T, bool KAHAN, bool PHI, bool UNIFORM, bool MASK, typename V4>
+__device__ inline void direct_pair(const V4 s, bool live, bool self, T eps2, Lane<T>& l) {
+  const T dx = l.x - s.x, dy = l.y - s.y, dz = l.z - s.z;
+  T r2 = n3_fma(dx, dx, eps2);
+  r2 = n3_fma(dy, dy, r2);
+  r2 = n3_fma(dz, dz, r2);
+  T qinv = 0, sc;
+  if (PHI || sizeof(T) == 4) {
+    T inv = n3_rsq(r2);
+    if (MASK && !live) inv = 0;
+    qinv = UNIFORM ? inv : s.w * inv;
+    sc = qinv * (inv * inv);
+  } else {
+    sc = n3_cubed(r2);
+    if (MASK && !live) sc = 0;
+    if (!UNIFORM) sc *= s.w;
+  }
+  add_term<T, KAHAN>(sc, dx, l.f[0], l.c[0]);
+  add_term<T, KAHAN>(sc, dy, l.f[1], l.c[1]);
+  add_term<T, KAHAN>(sc, dz, l.f[2], l.c[2]);
+  if (PHI) {
+    if (MASK && self) qinv = 0;
+    if (KAHAN) add_term<T, true>(qinv, T(1), l.f[3], l.c[3]);
+    else l.f[3] += qinv;
   }
 }
 
-// The lane's share of a chunk: sources grp, grp + 64, ... of the cnt in LDS; first is the place of
-// the lane's first target among them.
-template <typename T, int R, bool KAHAN, bool PHI, bool UNIFORM, bool MASK, typename V4>
-__device__ inline void direct_chunk(const V4* src, int cnt, int grp, int64_t first, T eps2, Lane<T, R>& l) {
-  const int whole = MASK ? 0 : cnt / kStep * kStep;
+// The lane's share of a chunk: sources grp, grp + STEP, ... of the cnt in LDS.  self is the place of
+// the lane's target among them; steps lo to hi hold the block's targets (the same in every lane).
+template <typename T, int STEP, bool KAHAN, bool PHI, bool UNIFORM, typename V4>
+__device__ inline void direct_chunk(const V4* src, int cnt, int grp, int lo, int hi, int self, T eps2, Lane<T>& l) {
+  const int whole = cnt / STEP * STEP;
+  lo = min(lo, whole);
 #pragma unroll 4
-  for (int k = grp; k < whole; k += kStep)
-    direct_pair<T, R, KAHAN, PHI, UNIFORM, false>(src[k], true, 0, eps2, l);
-  for (int k = whole; k < cnt; k += kStep) {
+  for (int k = 0; k < lo; k += STEP) direct_pair<T, KAHAN, PHI, UNIFORM, false>(src[k + grp], true, false, eps2, l);
+  for (int k = lo; k < min(hi, cnt); k += STEP) {
     const bool live = k + grp < cnt;
-    direct_pair<T, R, KAHAN, PHI, UNIFORM, true>(src[live ? k + grp : 0], live, MASK ? k + grp - first : -1, eps2, l);
+    direct_pair<T, KAHAN, PHI, UNIFORM, true>(src[live ? k + grp : 0], live, k + grp == self, eps2, l);
+  }
+#pragma unroll 4
+  for (int k = max(lo, hi); k < whole; k += STEP)
+    direct_pair<T, KAHAN, PHI, UNIFORM, false>(src[k + grp], true, false, eps2, l);
+  if (max(whole, hi) < cnt) {
+    const bool live = whole + grp < cnt;
+    direct_pair<T, KAHAN, PHI, UNIFORM, true>(src[live ? whole + grp : 0], live, false, eps2, l);
   }
 }
 
-template <typename T, int R, bool KAHAN, bool PHI>
-__global__ __launch_bounds__(kThreads) void k_field_direct(const double* __restrict__ xyzq, int64_t n, double eps2d,
-                                                           double* E, double* phi) {
+template <typename T, int COLS, int WAVES, bool KAHAN, bool PHI>
+__global__ __launch_bounds__(64 * WAVES) void k_field_direct(const double* __restrict__ xyzq, int64_t n,
+                                                             double eps2d, double* E, double* phi) {
   using V4 = typename N3Type<T>::V4;
-  constexpr int NC = PHI ? 4 : 3, TB = kCols * R;
+  constexpr int NC = PHI ? 4 : 3, GROUPS = 64 / COLS, STEP = GROUPS * WAVES, THREADS = 64 * WAVES;
   __shared__ V4 src[kChunk];
   double* red = reinterpret_cast<double*>(src);  // [wave][component][target], after the last chunk
-  static_assert(sizeof(double) * kWaves * 4 * TB <= sizeof(V4) * kChunk, "the block's partial sums fit");
+  static_assert(sizeof(double) * WAVES * 4 * COLS <= sizeof(V4) * kChunk, "the block's partial sums fit");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int t = lane % kCols, grp = kGroups * wave + lane / kCols;
+  const int t = lane % COLS, grp = GROUPS * wave + lane / COLS;
   const T eps2 = (T)eps2d;
-  for (int64_t i0 = (int64_t)blockIdx.x * TB; i0 < n; i0 += (int64_t)gridDim.x * TB) {
-    Lane<T, R> l;
+  for (int64_t i0 = (int64_t)blockIdx.x * COLS; i0 < n; i0 += (int64_t)gridDim.x * COLS) {
+    Lane<T> l;
+    const int64_t i = i0 + t < n ? i0 + t : n - 1;  // lanes past the last target repeat it and store nothing
+    l.x = (T)xyzq[i];
+    l.y = (T)xyzq[n + i];
+    l.z = (T)xyzq[2 * n + i];
+    double e[NC];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {  // lanes past the last target repeat it and store nothing
-      const int64_t i = i0 + t + kCols * r < n ? i0 + t + kCols * r : n - 1;
-      l.x[r] = (T)xyzq[i];
-      l.y[r] = (T)xyzq[n + i];
-      l.z[r] = (T)xyzq[2 * n + i];
-    }
-    double e[R][NC];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) e[r][k] = 0.0;
+    for (int k = 0; k < NC; ++k) e[k] = 0.0;
     for (int64_t j0 = 0; j0 < n; j0 += kChunk) {
       const int cnt = (int)(n - j0 < kChunk ? n - j0 : kChunk);
       const T q0 = (T)xyzq[3 * n + j0];
       int same = 1;
       __syncthreads();  // the sources and sums before these are read
-      for (int k = tid; k < cnt; k += kThreads) {
+      for (int k = tid; k < cnt; k += THREADS) {
         const int64_t j = j0 + k;
         V4 v;
         v.x = (T)xyzq[j];
@@ -137,47 +133,43 @@ __global__ __launch_bounds__(kThreads) void k_field_direct(const double* __restr
         src[k] = v;
       }
       const bool uniform = __syncthreads_and(same);
-      const bool own = PHI && j0 < i0 + TB && i0 < j0 + cnt;  // the block's targets are among the sources
+      // the steps that hold the block's targets (COLS divides STEP: one, or in another chunk none)
+      const bool own = PHI && i0 >= j0 && i0 < j0 + cnt;
+      const int lo = own ? (int)(i0 - j0) / STEP * STEP : kChunk, hi = own ? lo + STEP : 0;
+      const int self = own ? (int)(i - j0) : -1;
 #pragma unroll
-      for (int r = 0; r < R; ++r)
+      for (int k = 0; k < 4; ++k) l.f[k] = l.c[k] = 0;
+      if (uniform) direct_chunk<T, STEP, KAHAN, PHI, true>(src, cnt, grp, lo, hi, self, eps2, l);
+      else direct_chunk<T, STEP, KAHAN, PHI, false>(src, cnt, grp, lo, hi, self, eps2, l);
+      const double qs = uniform ? (double)q0 : 1.0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) l.f[r][k] = l.c[r][k] = 0;
-      if (own) direct_chunk<T, R, KAHAN, PHI, false, true>(src, cnt, grp, i0 + t - j0, eps2, l);
-      else if (uniform) direct_chunk<T, R, KAHAN, PHI, true, false>(src, cnt, grp, 0, eps2, l);
-      else direct_chunk<T, R, KAHAN, PHI, false, false>(src, cnt, grp, 0, eps2, l);
-      const double qs = uniform && !own ? (double)q0 : 1.0;
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int k = 0; k < NC; ++k) e[r][k] += (double)l.f[r][k] * qs;
+      for (int k = 0; k < NC; ++k) e[k] += (double)l.f[k] * qs;
     }
     __syncthreads();  // the last chunk is read
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        for (int o = kCols; o < 64; o <<= 1) e[r][k] += __shfl_xor(e[r][k], o, 64);
-        if (lane < kCols) red[(wave * NC + k) * TB + kCols * r + t] = e[r][k];
-      }
+    for (int k = 0; k < NC; ++k) {
+      for (int o = COLS; o < 64; o <<= 1) e[k] += __shfl_xor(e[k], o, 64);
+      if (lane < COLS) red[(wave * NC + k) * COLS + t] = e[k];
+    }
     __syncthreads();
-    for (int v = tid; v < NC * TB; v += kThreads) {
-      const int k = v / TB, i = v % TB;
+    for (int v = tid; v < NC * COLS; v += THREADS) {
+      const int k = v / COLS, c = v % COLS;
       double sum = 0.0;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) sum += red[(w * NC + k) * TB + i];
-      if (i0 + i < n) {
-        if (k < 3) E[k * n + i0 + i] = sum;
-        else phi[i0 + i] = sum;
+      for (int w = 0; w < WAVES; ++w) sum += red[(w * NC + k) * COLS + c];
+      if (i0 + c < n) {
+        if (k < 3) E[k * n + i0 + c] = sum;
+        else phi[i0 + c] = sum;
       }
     }
   }
 }
 
-template <typename T, bool KAHAN>
+template <typename T, int COLS, int WAVES, bool KAHAN>
 hipError_t launch_direct(int64_t n, const double* xyzq, double eps2, double* E, double* phi, hipStream_t st) {
-  const int grid = (int)std::min<int64_t>((n + kCols - 1) / kCols, kGrid);
-  if (phi) k_field_direct<T, 1, KAHAN, true><<<grid, kThreads, 0, st>>>(xyzq, n, eps2, E, phi);
-  else k_field_direct<T, 1, KAHAN, false><<<grid, kThreads, 0, st>>>(xyzq, n, eps2, E, phi);
+  const int grid = (int)std::min<int64_t>((n + COLS - 1) / COLS, kGrid);
+  if (phi) k_field_direct<T, COLS, WAVES, KAHAN, true><<<grid, 64 * WAVES, 0, st>>>(xyzq, n, eps2, E, phi);
+  else k_field_direct<T, COLS, WAVES, KAHAN, false><<<grid, 64 * WAVES, 0, st>>>(xyzq, n, eps2, E, phi);
   return hipGetLastError();
 }
 
@@ -389,11 +381,12 @@ hipError_t launch_pairs(int64_t n, const double* xyzq, double eps2, double* E, d
 
 }  // namespace
 
-// Each pair once from 3584 charges (14 blocks) on, as long as a strip can hold the rows of one J
-// (up to about a million charges).  Below, 105 tiles or fewer leave most of the chip idle: 3000
-// charges take 17 to 22 us each pair once and 14 to 19 us direct, 4099 take 18 to 24 us against 20
-// to 41 us.  Kahan sums have no form that takes each pair once.
-constexpr int64_t kPairsFrom = 3584;
+// Each pair once past 4096 charges, as long as a strip can hold the rows of one J (up to about a
+// million charges).  Up to there the direct kernel has one block of 16 targets per compute unit at
+// most (4096 charges with the potential: 13.1 us in FP32 and 18.6 us in FP64, each pair once 18.6 and
+// 22.2 us), beyond some have two (4099: 20.1 and 30.7 us against 18.8 and 22.2 us).  Kahan sums have
+// no form that takes each pair once.
+constexpr int64_t kPairsFrom = 16 * kUnits + 1;
 bool field_pairs(int precision, int64_t n) {
   if (precision == LC_FP32_KAHAN || n < kPairsFrom) return false;
   const int64_t nb = (n + kPB - 1) / kPB;
@@ -417,9 +410,16 @@ hipError_t launch_field_default(int precision, int64_t n, const double* xyzq, do
     return phi ? launch_pairs<float, true>(n, xyzq, eps2, E, phi, work, st)
                : launch_pairs<float, false>(n, xyzq, eps2, E, phi, work, st);
   }
-  if (precision == LC_FP64) return launch_direct<double, false>(n, xyzq, eps2, E, phi, st);
-  if (precision == LC_FP32_KAHAN) return launch_direct<float, true>(n, xyzq, eps2, E, phi, st);
-  return launch_direct<float, false>(n, xyzq, eps2, E, phi, st);
+  if (precision == LC_FP64) return launch_direct<double, 16, 16, false>(n, xyzq, eps2, E, phi, st);
+  if (precision != LC_FP32_KAHAN) return launch_direct<float, 16, 16, false>(n, xyzq, eps2, E, phi, st);
+  // Kahan sums of any size: up to a block of 16 targets per compute unit 16 waves each, beyond 8 waves
+  // (20,000 charges: 223 against 243 us) with 16 targets, or with 8 where the last round of blocks
+  // would leave more of the chip idle than their larger share of staging costs, about 8 % (4099: 21.3
+  // against 24.8 us, 8200: 56 and 60, 8192: 49 and 46 us)
+  const int64_t whole = (n + 16 * kUnits - 1) / (16 * kUnits), halves = (n + 8 * kUnits - 1) / (8 * kUnits);
+  if (whole == 1) return launch_direct<float, 16, 16, true>(n, xyzq, eps2, E, phi, st);
+  return 100 * 2 * whole <= 108 * halves ? launch_direct<float, 16, 8, true>(n, xyzq, eps2, E, phi, st)
+                                         : launch_direct<float, 8, 8, true>(n, xyzq, eps2, E, phi, st);
 }
 
 }  // namespace lc
