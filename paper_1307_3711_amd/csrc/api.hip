@@ -390,11 +390,15 @@ int choose_splits(const lc_sim* s, const ForceTiling& ft) {
 // scalar unit (a step of 1000: 13.4 against 14.1 us; of 3000 17.5 against 16.8, of 20,000 144
 // against 131); Kahan sums would meet a segment's padding in LDS, and a periodic pass factors equal
 // charges out of whole segments only there, so both stay there.
-// FP64: one target per lane, the block's four waves sharing its 64 targets, and enough splits for
-// about 4096 blocks (four waves for every SIMD), at most 16 and at least 8 where clusters are large
-// enough for the finer tail to pay, none below 128 sources; a pass over 36 clusters of 80 to 1000
-// macroparticles: 24.0 -> 18.8 us.  Clusters of 32,768 and more take four targets per lane and 16
-// splits (100,000: 6.1 against 6.2 ms; at 20,000 and below one target is as fast or faster).
+// FP64: one target per lane, the block's four waves sharing its 64 targets, and the most splits, up to
+// 16, that one of three aims asks for: two blocks per compute unit however few sources that leaves a
+// split (a step of 800 macroparticles 10.7 -> 9.5 us, of 8 clusters of 128 on average 11.6 -> 9.4 us
+// against splits of 128 sources), five blocks with 128 sources or more (36 clusters of 80 to 1000
+// 30.2 -> 28.8 us against 16 blocks, 100 of them 48.6 -> 41.5 us), sixteen with 512 or more, where a
+// finer tail pays (10,000: 74.6 against 75.5 us with eight).  At least 8 in clusters of 16,384 and
+// more.  A pass over the 36 clusters took 24.0 us with default_tiling.  Clusters of 32,768 and more
+// take four targets per lane and 16 splits (100,000: 6.1 against 6.2 ms; at 20,000 and below one target
+// is as fast or faster).
 ForceTiling auto_tiling(const lc_sim* s) {
   ForceTiling ft = default_tiling(s->cfg.precision);
   double s1 = 0.0, s2 = 0.0;
@@ -412,9 +416,11 @@ ForceTiling auto_tiling(const lc_sim* s) {
     ft.scalar_src = s->cfg.precision == LC_FP32_ACC64 && s->cfg.boundary == LC_OPEN && typical < 2048.0 ? 1 : 0;
     return ft;
   }
-  int64_t S = std::min<int64_t>(16, (4096 + blocks - 1) / blocks);
+  const int64_t sources = std::max<int64_t>(1, (int64_t)typical);
+  int64_t S = std::max({std::min(512 / blocks, sources / 16), std::min((1280 + blocks / 2) / blocks, sources / 128),
+                        std::min((4096 + blocks - 1) / blocks, sources / 512)});
   if (typical >= 16384.0) S = std::max<int64_t>(S, 8);
-  S = std::max<int64_t>(1, std::min<int64_t>(S, (int64_t)(typical / 128.0)));
+  S = std::max<int64_t>(1, std::min<int64_t>(S, 16));
   ft.R = 1;
   ft.WJ = 4;
   if (typical >= 32768.0 && s->cfg.max_splits >= 16) {
