@@ -22,13 +22,16 @@ __device__ inline double rsq64(double x) {
 // x^{-3/2} to FP64 rounding in six instructions after the estimate, one less than the cube of
 // rsq64: with Y = y0^2 rounded and e = 1 - x Y (exact up to one FMA rounding), x^{-3/2} =
 // Y^{3/2} (1 - e)^{-3/2} = Y^{3/2} (1 + 3e/2 + 15e^2/8 + O(e^3)), and Y y0 is Y^{3/2} to 1.5 roundings.
-// A field of 50,021 charges taken in pairs: 996 against 1053 us; 100 steps of the 20k argon cluster
-// 16.86 against 17.09 ms.
+// The series' FMA is written out: neither 3/2 nor 15/8 is an inline constant, and for the second one
+// the compiler copies 3/2 into the result's registers before every FMA (two of 26 instructions).
+// Measured on one card: a field of 50,021 charges taken in pairs 995 us, 1011 with the copies, 1053 with
+// the cube of rsq64; the pair-once pass of the 20k argon cluster 154.4 us, 157.5 with the copies.
 __device__ inline double rsq64_cubed(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double y2 = y * y;
   const double e = __builtin_fma(-x, y2, 1.0);
-  const double p = __builtin_fma(1.875, e, 1.5);
+  double p;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(p) : "v"(e), "s"(1.875), "v"(1.5));
   const double y3 = y2 * y;
   return __builtin_fma(y3 * e, p, y3);
 }
