@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblcmd.so")
-SOURCES = ["api.hip", "force.hip", "field.hip", "step.hip", "mlp.hip"]
+SOURCES = ["api.hip", "force.hip", "step.hip", "mlp.hip"]
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-fPIC", "-shared", "-std=c++17",
     "-ffp-contract=off", "-mcode-object-version=5",

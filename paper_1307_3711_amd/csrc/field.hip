@@ -3,12 +3,14 @@
 //
 //   E_i   = sum_{j != i} q_j (r_i - r_j) / (|r_i - r_j|^2 + eps^2)^{3/2}
 //   phi_i = sum_{j != i} q_j / (|r_i - r_j|^2 + eps^2)^{1/2}        (when asked for)
+// Part of force.hip's object: force.hip includes this file.
 #include <algorithm>
 
 #include "lc_internal.h"
 #include "pair_math.h"
 
 namespace lc {
+namespace field_default {
 namespace {
 
 // One launch, straight from the caller's arrays to the caller's results.  A block of WAVES waves takes
@@ -380,6 +382,9 @@ hipError_t launch_pairs(int64_t n, const double* xyzq, double eps2, double* E, d
 }
 
 }  // namespace
+}  // namespace field_default
+
+using namespace field_default;
 
 // Each pair once past 4096 charges, as long as a strip can hold the rows of one J (up to about a
 // million charges).  Up to there the direct kernel has one block of 16 targets per compute unit at

@@ -414,7 +414,7 @@ __device__ void tile_f64(const ForceArgs<double4>& a, int t, double4* lds) {
               qinv = sj.w * inv;
               sc = qinv * (inv * inv);
             } else {
-              sc = sj.w * rsq64_cubed(r2);
+              sc = sj.w * rsq64_cubed<true>(r2);
             }
             ex[r] = __builtin_fma(sc, dx, ex[r]);
             ey[r] = __builtin_fma(sc, dy, ey[r]);
@@ -1257,3 +1257,5 @@ hipError_t launch_field_standalone(int precision, int64_t n, const double* xyzq,
 }
 
 }  // namespace lc
+
+#include "field.hip"  // the standalone field with the default tiling

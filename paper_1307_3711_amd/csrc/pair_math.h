@@ -26,12 +26,15 @@ __device__ inline double rsq64(double x) {
 // the compiler copies 3/2 into the result's registers before every FMA (two of 26 instructions).
 // Measured on one card: a field of 50,021 charges taken in pairs 995 us, 1011 with the copies, 1053 with
 // the cube of rsq64; the pair-once pass of the 20k argon cluster 154.4 us, 157.5 with the copies.
+// A loop with the written-out FMA is not unrolled any more, so WRITTEN is for loops that unroll by hand.
+template <bool WRITTEN>
 __device__ inline double rsq64_cubed(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double y2 = y * y;
   const double e = __builtin_fma(-x, y2, 1.0);
   double p;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(p) : "v"(e), "s"(1.875), "v"(1.5));
+  if (WRITTEN) asm("v_fma_f64 %0, %1, %2, %3" : "=v"(p) : "v"(e), "s"(1.875), "v"(1.5));
+  else p = __builtin_fma(1.875, e, 1.5);
   const double y3 = y2 * y;
   return __builtin_fma(y3 * e, p, y3);
 }
@@ -58,7 +61,7 @@ __device__ inline float n3_cubed(float x) {
   const float inv = rsq32(x);
   return inv * (inv * inv);
 }
-__device__ inline double n3_cubed(double x) { return rsq64_cubed(x); }
+__device__ inline double n3_cubed(double x) { return rsq64_cubed<false>(x); }
 
 __device__ inline float n3_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ inline double n3_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -130,7 +133,8 @@ __device__ inline void n3_steps(const T* bx, const T* by, const T* bz, const T* 
         inv = n3_rsq(r2);
         r3 = inv * (inv * inv);
       } else {
-        r3 = n3_cubed(r2);
+        if constexpr (sizeof(T) == 4) r3 = n3_cubed(r2);
+        else r3 = rsq64_cubed<true>(r2);
       }
       const T si = US ? r3 : bq[u] * r3;
       fx[r] = n3_fma(si, dx, fx[r]);
