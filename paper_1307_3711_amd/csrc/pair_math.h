@@ -111,6 +111,17 @@ __device__ inline void wave_lds_sync() {
 constexpr int kN3Slice = 136;
 __host__ __device__ constexpr int n3_slices(int waves) { return waves * 4 * kN3Slice; }  // elements
 
+// Between the stages of FP32 pair terms: keeps the reciprocal roots of a group of pairs together.
+// FP32 instructions with vector operands go out for two waves of a SIMD at a time (2.4 to 2.9 cycles
+// each with two waves or more; 4.2 with a scalar operand or DPP, 8.2 for v_rsq_f32), and a lone
+// v_rsq_f32 among them costs about 30: a loop of the pair-once instructions takes 72 cycles a pair with
+// its roots spread out, as the compiler schedules them, and 55 with eight of them in a row.  The
+// pair-once pass of the 20k argon cluster: 91.9 -> 87.4 us, of 199,998 macroparticles 7.65 -> 7.28 ms.
+template <typename T>
+__device__ inline void rsq_fence() {
+  if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0x94);
+}
+
 // U rotations of the chunk from the register buffers (bx, by, bz, bq) holding their sources.
 // PHI: also the potential, fp of the targets and (JSIDE) rp of the sources; self: the r whose
 // target is the first rotation's source (-1: none), which its own potential leaves out.
@@ -118,46 +129,65 @@ template <typename T, int R, int U, bool US, bool UT, bool JSIDE, bool PBC, bool
 __device__ inline void n3_steps(const T* bx, const T* by, const T* bz, const T* bq, const T* xi, const T* yi,
                                 const T* zi, const T* qi, T eps2f, T* fx, T* fy, T* fz, T& rx, T& ry, T& rz, T L,
                                 T iL, T* fp = nullptr, T* rp = nullptr, int self = -1) {
+  constexpr int G = sizeof(T) == 4 && R * U <= 8 ? U : 1;  // rotations and targets of a group
+  constexpr int GR = sizeof(T) == 4 ? R : 1;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
+  for (int u0 = 0; u0 < U; u0 += G) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T dx = pair_sep<T, PBC>(xi[r], bx[u], L, iL);
-      const T dy = pair_sep<T, PBC>(yi[r], by[u], L, iL);
-      const T dz = pair_sep<T, PBC>(zi[r], bz[u], L, iL);
-      T r2 = n3_fma(dx, dx, eps2f);
-      r2 = n3_fma(dy, dy, r2);
-      r2 = n3_fma(dz, dz, r2);
-      T inv, r3;
-      if constexpr (PHI) {
-        inv = n3_rsq(r2);
-        r3 = inv * (inv * inv);
-      } else {
-        if constexpr (sizeof(T) == 4) r3 = n3_cubed(r2);
-        else r3 = rsq64_cubed<true>(r2);
+    for (int r0 = 0; r0 < R; r0 += GR) {
+      T dx[G][GR], dy[G][GR], dz[G][GR], inv[G][GR];
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+#pragma unroll
+        for (int r = 0; r < GR; ++r) {
+          dx[u][r] = pair_sep<T, PBC>(xi[r0 + r], bx[u0 + u], L, iL);
+          dy[u][r] = pair_sep<T, PBC>(yi[r0 + r], by[u0 + u], L, iL);
+          dz[u][r] = pair_sep<T, PBC>(zi[r0 + r], bz[u0 + u], L, iL);
+          T r2 = n3_fma(dx[u][r], dx[u][r], eps2f);
+          r2 = n3_fma(dy[u][r], dy[u][r], r2);
+          inv[u][r] = n3_fma(dz[u][r], dz[u][r], r2);
+        }
       }
-      const T si = US ? r3 : bq[u] * r3;
-      fx[r] = n3_fma(si, dx, fx[r]);
-      fy[r] = n3_fma(si, dy, fy[r]);
-      fz[r] = n3_fma(si, dz, fz[r]);
-      if (JSIDE) {
-        const T sr = UT ? r3 : qi[r] * r3;
-        rx = n3_fma(sr, dx, rx);
-        ry = n3_fma(sr, dy, ry);
-        rz = n3_fma(sr, dz, rz);
+      if constexpr (sizeof(T) == 4 || PHI) {
+        rsq_fence<T>();
+#pragma unroll
+        for (int u = 0; u < G; ++u)
+#pragma unroll
+          for (int r = 0; r < GR; ++r) inv[u][r] = n3_rsq(inv[u][r]);
+        rsq_fence<T>();
       }
-      if constexpr (PHI) {
-        T pi = US ? inv : bq[u] * inv;
-        if (!JSIDE && u == 0 && r == self) pi = 0;
-        fp[r] += pi;
-        if (JSIDE) *rp = UT ? *rp + inv : n3_fma(qi[r], inv, *rp);
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+#pragma unroll
+        for (int r = 0; r < GR; ++r) {
+          const int k = r0 + r;
+          T r3;
+          if constexpr (sizeof(T) == 4 || PHI) r3 = inv[u][r] * (inv[u][r] * inv[u][r]);
+          else r3 = rsq64_cubed<true>(inv[u][r]);
+          const T si = US ? r3 : bq[u0 + u] * r3;
+          fx[k] = n3_fma(si, dx[u][r], fx[k]);
+          fy[k] = n3_fma(si, dy[u][r], fy[k]);
+          fz[k] = n3_fma(si, dz[u][r], fz[k]);
+          if (JSIDE) {
+            const T sr = UT ? r3 : qi[k] * r3;
+            rx = n3_fma(sr, dx[u][r], rx);
+            ry = n3_fma(sr, dy[u][r], ry);
+            rz = n3_fma(sr, dz[u][r], rz);
+          }
+          if constexpr (PHI) {
+            T pi = US ? inv[u][r] : bq[u0 + u] * inv[u][r];
+            if (!JSIDE && u0 + u == 0 && k == self) pi = 0;
+            fp[k] += pi;
+            if (JSIDE) *rp = UT ? *rp + inv[u][r] : n3_fma(qi[k], inv[u][r], *rp);
+          }
+        }
+        if (JSIDE && r0 + GR == R) {
+          if constexpr (PHI) *rp = wave_rol1(*rp);
+          rx = wave_rol1(rx);
+          ry = wave_rol1(ry);
+          rz = wave_rol1(rz);
+        }
       }
-    }
-    if (JSIDE) {
-      if constexpr (PHI) *rp = wave_rol1(*rp);
-      rx = wave_rol1(rx);
-      ry = wave_rol1(ry);
-      rz = wave_rol1(rz);
     }
   }
 }
@@ -185,7 +215,7 @@ template <typename T, int R, bool US, bool UT, bool JSIDE, bool PBC, bool PHI = 
 __device__ inline void n3_chunk(const T* sb, int lane, const T* xi, const T* yi, const T* zi, const T* qi, T eps2f,
                                 T* fx, T* fy, T* fz, T& ax, T& ay, T& az, T L, T iL, T* fp = nullptr,
                                 T* ap = nullptr, int self = -1) {
-  constexpr int U = (R >= 4 || sizeof(T) == 8) ? 2 : 4;  // rotations per register buffer
+  constexpr int U = (R >= 2 || sizeof(T) == 8) ? 2 : 4;  // rotations per register buffer
   static_assert(128 + U <= kN3Slice && 64 % (2 * U) == 0, "prefetch stays inside the wave's slice");
   const T* sx = sb + lane;
   T rx = 0, ry = 0, rz = 0, rp = 0;  // running sums of source (lane + k) mod 64
