@@ -76,11 +76,16 @@ def counter_record(tuned, n, precision="fp32_acc64", boundary="open"):
     path = os.path.join(ROOT, "profiles", "k_force_ar20k_counters.json")
     try:
         recs = json.load(open(path))["records"]
-        digest = kernel_code_digest(os.path.join(ROOT, "paper_1307_3711_amd", "csrc", "force.hip"))
+        csrc = os.path.join(ROOT, "paper_1307_3711_amd", "csrc")
+        digest = kernel_code_digest(os.path.join(csrc, "force.hip"))
+        pair_math = os.path.join(csrc, "pair_math.h")  # the pair terms, included by force.hip
+        pair_digest = kernel_code_digest(pair_math) if os.path.exists(pair_math) else None
     except (OSError, KeyError, ValueError):
         return None
     for rec in recs:
         if rec.get("force_hip_code_sha256") != digest or rec["n_particles"] != n:
+            continue
+        if rec.get("pair_math_code_sha256") != pair_digest:
             continue
         if rec.get("precision", "fp32_acc64") != precision or rec.get("boundary", "open") != boundary:
             continue

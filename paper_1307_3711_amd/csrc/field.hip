@@ -182,10 +182,10 @@ hipError_t launch_direct(int64_t n, const double* xyzq, double eps2, double* E, 
 // strips of J so that a strip's rows fit the workspace: row (I, J) of the strip from J0 sits at
 // J^2 - J0^2 + I, row (J, I) at J^2 - J0^2 + J + 1 + I, and a fold after each strip adds a charge's
 // rows in a fixed order in FP64, and to the result of the strips before.
-// VALU-bound (force.hip has the count of its instructions); the potential adds two per evaluation.
-// Measured a call, field and potential: 20,000 charges in FP32 134 us, in FP64 205 us; 50,021 in
-// FP64 without it 1117 us, in five strips, against 2699, 1040 and 5245 us before; the one-sided kernels at their best tilings take 158, 311
-// and 1843 us.
+// Bound by VALU issue (pair_math.h has the rates); the potential adds two instructions a pair.  Measured
+// a call: 20,000 charges with the potential in FP32 122 us, in FP64 196 us; 50,021 in FP64 without it
+// 985 us, in four strips, against 2699, 1040 and 5245 us before; the one-sided kernels at their best
+// tilings take 158, 311 and 1843 us.
 constexpr int kPR = 4, kPB = 64 * kPR;  // targets per lane, charges per block
 
 template <typename T, bool PHI>

@@ -132,7 +132,7 @@ __device__ inline T pass_eps2(double eps2, double box) {
 // has the same charge q0 and the caller multiplies the sums by it (q r^-3 costs one multiply
 // less per pair).  PHI: also the potential, with the self pair masked out by index (MASK: the
 // sources include the lane's targets; elsewhere the compare and the select, two of 18 issue slots,
-// are left out: with the potential a pass over 200,000 macroparticles takes 11.83 ms instead of 13.46).
+// are left out: with the potential a pass over 200,000 macroparticles took 11.83 ms instead of 13.46).
 // src is an LDS tile, or a global source array read with wave-uniform indices (the compiler
 // then issues scalar loads and the pair arithmetic takes SGPR operands).  The sums and the
 // Kahan compensations (cx..cpc) accumulate onto the caller's registers.
