@@ -770,7 +770,8 @@ __global__ __launch_bounds__(64 * kFoldWaves) void k_fold_n3(DevState s, RunCons
 // ----------------------------------------------------------------------------- kernels
 // Occupancy the register allocation aims at: 5 waves per SIMD for FP32 pairs (96 VGPRs at R = WJ =
 // 4, three values of some pair loops spilled; 20,000 macroparticles 87.1 us, with 4 waves and no spills
-// 90.9; 4 from R = 6 and at R = 4, WJ = 2: 110.8 against 112.1 us), 3 for FP64 pairs (twice the registers per value; 2 from R = 5).
+// 90.9; 4 from R = 6 and at R = 4, WJ = 2: 110.8 against 112.1 us), 3 for FP64 pairs (twice the
+// registers per value; 2 from R = 5).
 template <typename T, int R, int WJ, bool PBC>
 __global__ __launch_bounds__(64 * n3_waves(R, WJ))
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (R >= 5 ? 2 : 3) : (R >= 6 || (R == 4 && WJ == 2) ? 4 : 5))))
