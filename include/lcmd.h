@@ -356,7 +356,9 @@ size_t lc_field_workspace_bytes(int32_t precision, int64_t n, const lc_tuning* t
  *   phi_i = sum_{j != i} q_j / (|r_i - r_j|^2 + eps^2)^{1/2}        (if d_phi != NULL)
  * d_xyzq: device, 4 n doubles laid out x[n], y[n], z[n], q[n] (q in field units).
  * d_E: device, 3 n doubles out, laid out Ex[n], Ey[n], Ez[n].  d_work: caller-owned device
- * workspace of at least lc_field_workspace_bytes().  Asynchronous on hip_stream.
+ * workspace of at least lc_field_workspace_bytes().  Asynchronous on hip_stream.  d_E and d_phi
+ * may lie over d_xyzq (not over each other or d_work): a default call (t = NULL or all zeros)
+ * then runs the one-sided kernel, with its results.
  * A tiling with newton3 = 1 computes E only (d_phi must be NULL).
  * LC_E_INVALID for n < 0, n > 2^30, eps2 <= 0, a workspace that is too small or not 256-byte
  * aligned, or an unknown tiling; LC_E_HIP when a launch fails (also for a request of more than

@@ -1542,6 +1542,25 @@ int field_args_ok(int32_t precision, int64_t n, const double* d_xyzq, double eps
   return 1;
 }
 
+// Whether a result of the call lies over its charges.
+bool field_in_place(int64_t n, const double* d_xyzq, const double* d_E, const double* d_phi) {
+  const uintptr_t a = (uintptr_t)d_xyzq, len = sizeof(double) * (uintptr_t)n;
+  auto over = [&](const double* p, uintptr_t bytes) {
+    const uintptr_t b = (uintptr_t)p;
+    return p && b < a + 4 * len && a < b + bytes;
+  };
+  return over(d_E, 3 * len) || over(d_phi, len);
+}
+
+// A default call goes to field.hip's kernels.  They read the caller's charges while they write results,
+// so a call in place takes the one-sided kernel, which reads copies of them in the workspace.
+hipError_t launch_field(int precision, int64_t n, const double* xyzq, double eps2, double* E, double* phi, void* work,
+                        size_t work_bytes, const lc_tuning* t, const ForceTiling& ft, hipStream_t st) {
+  if (tuning_default(t) && !field_in_place(n, xyzq, E, phi))
+    return launch_field_default(precision, n, xyzq, eps2, E, phi, work, work_bytes, st);
+  return launch_field_standalone(precision, n, xyzq, eps2, E, phi, work, ft, st);
+}
+
 }  // namespace
 
 int lc_field(int32_t precision, int64_t n, const double* d_xyzq, double eps2, double* d_E, double* d_phi,
@@ -1551,9 +1570,8 @@ int lc_field(int32_t precision, int64_t n, const double* d_xyzq, double eps2, do
   if (n > 0 && !d_work) return LC_E_INVALID;
   if (((uintptr_t)d_work & 255) != 0) return LC_E_INVALID;
   if (work_bytes < field_workspace_bytes(precision, n, ft)) return LC_E_INVALID;
-  hipError_t e = tuning_default(t)
-                     ? launch_field_default(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, work_bytes, (hipStream_t)hip_stream)
-                     : launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, ft, (hipStream_t)hip_stream);
+  const hipError_t e = launch_field(precision, n, d_xyzq, eps2, d_E, d_phi, d_work, work_bytes, t, ft,
+                                    (hipStream_t)hip_stream);
   return e == hipSuccess ? LC_OK : LC_E_HIP;
 }
 
@@ -1566,9 +1584,8 @@ int lc_field_static(int32_t precision, int64_t n, const double* d_xyzq, double e
   void* work = nullptr;
   hipError_t e = field_scratch(&work);
   if (e == hipSuccess)
-    e = tuning_default(t) ? launch_field_default(precision, n, d_xyzq, eps2, d_E, d_phi, work, LC_FIELD_STATIC_MAX_BYTES,
-                                                (hipStream_t)hip_stream)
-                         : launch_field_standalone(precision, n, d_xyzq, eps2, d_E, d_phi, work, ft, (hipStream_t)hip_stream);
+    e = launch_field(precision, n, d_xyzq, eps2, d_E, d_phi, work, LC_FIELD_STATIC_MAX_BYTES, t, ft,
+                     (hipStream_t)hip_stream);
   return e == hipSuccess ? LC_OK : LC_E_HIP;
 }
 
