@@ -317,6 +317,7 @@ struct lc_sim {
   hipGraph_t graph = nullptr;
   std::string last_error;
   Units u;
+  int device = 0;           // the device that holds d_state
   ReadBuffer rb;            // pinned, from the first read-out on
 };
 
@@ -539,6 +540,31 @@ void free_read_buffer(lc_sim* s) {
   s->rb = ReadBuffer{};
 }
 
+// The device that memory lies on (the current one if the runtime does not know it).
+int device_of(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.device;
+  (void)hipGetLastError();
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return dev;
+}
+
+// Makes a device the current one for a scope: an event belongs to the device it was created on, and
+// the null stream to the current one, while a copy finds its device by the address.
+struct OnDevice {
+  int before = 0;
+  bool changed = false;
+  explicit OnDevice(int dev) {
+    changed = hipGetDevice(&before) == hipSuccess && before != dev && hipSetDevice(dev) == hipSuccess;
+  }
+  ~OnDevice() {
+    if (changed) (void)hipSetDevice(before);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
+
 hipError_t read_buffer(lc_sim* s) {
   if (s->rb.head) return hipSuccess;
   const size_t head = al(sizeof(ReadHead)), area = al((size_t)kReadBytes);
@@ -562,6 +588,7 @@ hipError_t read_buffer(lc_sim* s) {
 // them.  The next packing runs while one is stored.
 template <typename C, typename P, typename T>
 hipError_t read_packed(lc_sim* s, int64_t chunk, int64_t* total, C count, P pack, T take) {
+  const OnDevice on(s->device);
   hipError_t e = read_buffer(s);
   if (e != hipSuccess) return e;
   pack((int64_t)0, s->rb.area[0]);
@@ -660,6 +687,7 @@ int lc_create(lc_sim** out, const lc_config* cfg, const lc_cluster* clusters, in
   s->cl.assign(clusters, clusters + n_clusters);
   s->C = n_clusters;
   s->stream = (hipStream_t)hip_stream;
+  s->device = device_of(d_state);
   s->L = L;
   s->u = make_units(cfg->lambda_um);
   s->n_host.assign(n_clusters, 0);
