@@ -589,7 +589,11 @@ hipError_t read_buffer(lc_sim* s) {
 template <typename C, typename P, typename T>
 hipError_t read_packed(lc_sim* s, int64_t chunk, int64_t* total, C count, P pack, T take) {
   const OnDevice on(s->device);
-  hipError_t e = read_buffer(s);
+  // a stream under capture cannot be waited for: refused before anything is recorded or allocated
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s->stream, &capture);
+  if (e != hipSuccess || capture != hipStreamCaptureStatusNone) e = hipStreamSynchronize(s->stream);
+  if (e == hipSuccess) e = read_buffer(s);
   if (e != hipSuccess) return e;
   pack((int64_t)0, s->rb.area[0]);
   e = hipGetLastError();

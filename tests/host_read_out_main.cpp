@@ -1,6 +1,6 @@
 // Read-outs against a HIP runtime that this file stands in for: two devices whose memory is the
 // host's, streams that know their device, and kernels that do not run except for the packing of
-// particles, which reports a live count.  Prints "bad 0" if every check held.
+// particles and records, of which the first reports a live count.  Prints "bad 0" if every check held.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -79,8 +79,10 @@ hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream
   return hipErrorNotSupported;
 }
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s) {
-  if (g_kernels[f].find("k_pack_particles") == std::string::npos) return hipSuccess;
+  const std::string& name = g_kernels[f];
+  if (name.find("k_pack_") == std::string::npos) return hipSuccess;
   ++g_packs;
+  if (name.find("k_pack_particles") == std::string::npos) return hipSuccess;
   if (device_of(s) != g_state_device) ++g_packs_elsewhere;
   lc::ClusterDyn* head = *(lc::ClusterDyn**)args[4];  // the read-out's head starts with the cluster's counts
   std::memset(head, 0, sizeof *head + sizeof(int32_t));
@@ -170,6 +172,22 @@ int main() {
     g_current = 0;
     lc_destroy(sim);
   }
+  // under capture a read-out is refused: nothing recorded into the graph, nothing allocated
+  g_current = 1;
+  lc_sim* sim = handle(n, (hipStream_t)&dev1, mem);
+  if (!sim) return 1;
+  g_packs = g_host_mallocs = 0;
+  dev1.capturing = true;
+  int64_t got = -1;
+  int32_t records = -1;
+  check(lc_read_particles(sim, 0, x.data(), nullptr, nullptr, nullptr, nullptr, n, &got) == LC_E_HIP && got == -1,
+        "particles refused under capture");
+  check(lc_read_diagnostics(sim, 0, x.data(), 1, &records) == LC_E_HIP && records == -1, "records refused under capture");
+  check(g_packs == 0 && g_host_mallocs == 0, "nothing recorded or allocated under capture");
+  dev1.capturing = false;
+  check(lc_read_particles(sim, 0, x.data(), nullptr, nullptr, nullptr, nullptr, n, &got) == LC_OK && got == n,
+        "particles read after the capture");
+  lc_destroy(sim);
   std::printf("bad %d\n", bad);
   return bad;
 }

@@ -1,5 +1,6 @@
-"""Read-outs of a handle whose device is not the current one: the library's objects linked against a
-stand-in HIP runtime with two devices (tests/host_read_out_main.cpp), which needs no GPU."""
+"""Read-outs of a handle whose device is not the current one, or whose stream is under capture: the
+library's objects linked against a stand-in HIP runtime with two devices (tests/host_read_out_main.cpp),
+which needs no GPU."""
 import os
 import shutil
 import subprocess
