@@ -213,7 +213,7 @@ void k_field_pairs(const double* __restrict__ xyzq, int64_t n, double eps2d, T* 
   const double *X = xyzq, *Y = xyzq + n, *Z = xyzq + 2 * n, *Q = xyzq + 3 * n;
   const int64_t i0 = I * kPB, jb = J * kPB + w * 64;
 
-  // the lane's targets; places past the last charge lie so far away that they add exactly zero
+  // the lane's targets; places past the last charge lie so far away that they add nothing to a field
   const T qT = (T)Q[i0];
   T xi[R], yi[R], zi[R], qi[R];
   int same_t = 1;
@@ -242,7 +242,9 @@ void k_field_pairs(const double* __restrict__ xyzq, int64_t n, double eps2d, T* 
     const T q0 = (T)Q[jb];
     const T x = live ? (T)X[j] : kFar, y = live ? (T)Y[j] : kFar, z = live ? (T)Z[j] : kFar;
     const T q = live ? (T)Q[j] : T(0);
-    const bool us = __all(!live || q == q0);
+    // with the potential in FP64 a place past the last charge is one of charge 0: its 1/r of 1e-150 would
+    // count among equal charges (FP32: 1/r is zero)
+    const bool us = __all(PHI && sizeof(T) == 8 ? live && q == q0 : !live || q == q0);
     T* sb = s.slice[w];
     sb[lane] = sb[lane + 64] = x;
     sb[kN3Slice + lane] = sb[kN3Slice + lane + 64] = y;

@@ -43,9 +43,10 @@ __device__ inline float n3_rsq(float x) { return rsq32(x); }
 __device__ inline double n3_rsq(double x) { return rsq64(x); }
 
 // Pair arithmetic of the pair-once kernel: float (LC_FP32_ACC64) or double (LC_FP64).
-// kFar places padding entries so far away that every term they take part in is exactly zero:
+// kFar places padding entries so far away that every field term they take part in is exactly zero:
 // FP32 r^2 overflows to +inf and v_rsq_f32(+inf) = +0; FP64 r^2 = 1e300 stays finite (the
-// refined 1/sqrt needs a finite argument) and (1/r)^3 = 1e-450 underflows to zero.
+// refined 1/sqrt needs a finite argument) and (1/r)^3 = 1e-450 underflows to zero.  A potential
+// term is zero in FP32; in FP64 it is 1e-150 times the charge, which the caller keeps at zero.
 template <typename T> struct N3Type;
 template <> struct N3Type<float> {
   using V4 = float4;
