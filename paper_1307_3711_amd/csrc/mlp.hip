@@ -137,20 +137,25 @@ __device__ inline void put_small(TrainLds& w, int wave, int lane, float p) {
   else w.b1[lane] = p;
 }
 
-// 1 / (1 + expf(-z)) in 18 issue slots instead of 29, the same bits (every FP32 argument of the two
-// parts was compared on the device): expf by its reduction x log2 e = n + a with the clamp in
-// place of its range checks (outside it the power is 0 or below an ulp of the 1, or infinite);
-// the reciprocal of a number in [1, 2^126] is correctly rounded after one Newton step, div_fixup
-// gives 0 for infinity.  Beyond 2^126 (z below -87) the subnormal quotient becomes 0.
+// 1 / (1 + expf(-z)) in 19 issue slots instead of 29, the same bits: expf by the usual reduction in
+// extended precision (the product x log2 e and its rounding error by a fused multiply-add, the nearest
+// integer, the power of the rest) with the clamp in place of its range checks (outside it the power is 0
+// or below an ulp of the 1, or infinite); the reciprocal of a number in [1/4, 2^126] is correctly
+// rounded after one Newton step, div_fixup gives 0 for infinity.  A quarter of the denominator is
+// inverted, so that the reciprocal stays above the subnormal numbers, which v_rcp_f32 flushes.  Compared
+// on the device for every FP32 argument: equal but where the result is subnormal (z below -87.3), there
+// 34,043 results are rounded twice and are off by one unit of the smallest subnormal number.  A NaN gives
+// a number; every use multiplies it by z.
 __device__ inline float sigmoid_train(float z) {
   constexpr float kLog2e = 1.44269502f, kLog2eLow = 1.9259629e-8f;
   const float x = __builtin_amdgcn_fmed3f(-z, -104.0f, 89.0f);
   const float p = x * kLog2e;
   const float low = __builtin_fmaf(x, kLog2eLow, __builtin_fmaf(x, kLog2e, -p));
   const float n = __builtin_rintf(p);
-  const float d = 1.0f + __builtin_ldexpf(__builtin_amdgcn_exp2f((p - n) + low), (int)n);
+  const float e = __builtin_ldexpf(__builtin_amdgcn_exp2f((p - n) + low), (int)n);
+  const float d = __builtin_fmaf(e, 0.25f, 0.25f);
   const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), d, 1.0f);
+  return 0.25f * __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), d, 1.0f);
 }
 
 // a / b with r the correctly rounded 1 / b: correctly rounded.
