@@ -4,8 +4,9 @@
 // Number formats: FP32 master weights and Adam moments; BF16 copies of the weights, the
 // inputs, both hidden activations and the back-propagated hidden-2 gradient feed the
 // products; every product accumulates in FP32.  The 64x64 layer (forward, input-gradient and
-// weight-gradient products) runs on v_mfma_f32_16x16x32_bf16; the 4-wide input layer and the
-// 2-wide output layer are VALU dot products.
+// weight-gradient products) runs on v_mfma_f32_16x16x32_bf16, the 4-wide input layer on
+// v_mfma_f32_16x16x4_f32; the 2-wide output layer is a VALU dot product in training and runs on
+// v_mfma_f32_16x16x32_bf16 in inference.
 //
 // MFMA 16x16x32 BF16 operand layout (checked on the device): lane l holds
 //   A[l % 16][8 (l / 16) + i], B[8 (l / 16) + i][l % 16] for i = 0..7, and the result
@@ -62,8 +63,6 @@ size_t carve(void* base, MlpState* s) {
   if (s) *s = t;
   return o;
 }
-
-__device__ inline float sigmoidf_(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 __device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -505,23 +504,37 @@ __global__ __launch_bounds__(kScalerThreads) void k_mlp_scaler(MlpState s, const
 }
 
 // ----------------------------------------------------------------------------- inference
-// SiLU for the inference kernel, z / (1 + 2^(-z log2 e)) on the hardware's power and reciprocal: 7
-// issue slots instead of 30 for 1 / (1 + expf(-z)) times z.  Its result is rounded to BF16 at once;
-// infinities and NaN come out as there (+inf: +inf, large negative: -0, -inf and NaN: NaN).
-__device__ inline float silu_fast(float z) {
-  return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z * -1.44269502f));
+// SiLU for the inference kernel, as exact as z times 1 / (1 + expf(-z)) in 15 issue slots instead of 30.
+// With x = -z: x log2 e = n + f, where n comes from adding a number with an ulp of one, and f from two
+// fused multiply-adds with log2 e in two parts; 2^f / 4 with the exponent n - 2 added to its bits; the
+// reciprocal of (1 + e^x) / 4, correctly rounded after one Newton step.  A quarter keeps the reciprocal
+// above the subnormal numbers, which v_rcp_f32 flushes, until 1 + e^x is infinite: there it gives 0.
+// Clamped where e^x no longer counts beside the 1, and where it is infinite; infinities and NaN come out
+// as of the plain form (+inf: +inf, large negative: -0, -inf and NaN: NaN).  Against 64 bits, over
+// every FP32 z above -87 the largest relative error is 1.47e-7 for z > 4, 1.83e-7 for |z| < 4, 1.75e-7
+// down to -10, 2.00e-7 to -30 and 1.60e-7 to -87, that of the plain form 1.47, 1.84, 1.75, 2.00 and 1.63;
+// the first part of log2 e is one of five tried that keep below it.  (With the hardware's power of
+// the rounded product and its reciprocal alone, 7 slots, it was 3.7e-7, 5.9e-7, 1.8e-6 and 3.9e-6.)
+__device__ inline float silu(float z) {
+  constexpr float kLog2e = 1.44269502f, kHigh = 1.44269562f, kLow = -5.76786817e-7f;
+  constexpr float kShift = 12582910.0f;  // 1.5 2^23 - 2: the low bits of a sum with it are n - 2
+  const float x = __builtin_amdgcn_fmed3f(-z, -80.0f, 88.8f);
+  const float t = __builtin_fmaf(x, kLog2e, kShift);
+  const float f = __builtin_fmaf(x, kLow, __builtin_fmaf(x, kHigh, kShift - t));
+  const float e = __uint_as_float((__float_as_uint(t) << 23) + __float_as_uint(__builtin_amdgcn_exp2f(f)));
+  const float d = e + 0.25f;
+  const float r = __builtin_amdgcn_rcpf(d);
+  return z * (0.25f * __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r));
 }
 
 // A wave walks over tiles of 16 rows with every weight in registers: layer 1 on the FP32 matrix
 // units (K = 4 is the input width: lane l brings input l / 16 of row l % 16, one coalesced load),
-// layers 2 and 3 on the BF16 ones, the SiLU on the VALU, which bounds it (about 300 issue slots a
-// tile: 30 us for a million rows; the 24 MB they move take 5 us).  No LDS and no barrier in the
-// loop.  Measured on a million rows: 52.8 us, against 437 us with the weights staged and converted
-// for every 64 rows, the inputs standardized once per unit and the outer layers on the VALU, and
-// 71 us with the rounding error of the exponent carried into the power.  Against the network in
-// FP64 the outputs of all three are off by the same 1.1e-4 (2-norm, BF16 rounding), equal to 1e-5
-// of that over seven sets of 100 to 2,000,000 rows.
-constexpr int kInferBlocks = 256 * 4;  // four blocks of four waves fit on each compute unit at 108 VGPRs
+// layers 2 and 3 on the BF16 ones, the SiLU on the VALU, which bounds it (32 of them are 480 of about
+// 560 issue slots a tile: 57 us for a million rows; the 24 MB they move take 5 us).  No LDS and no
+// barrier in the loop.  Measured on a million rows, back to back: 70.8 us, against 398 us with the weights
+// staged and converted for every 64 rows, the inputs standardized once per unit and the outer layers on
+// the VALU, 83.5 us with the SiLU of the training kernel, and 47 us with the less exact one.
+constexpr int kInferBlocks = 256 * 4;  // four blocks of four waves fit on each compute unit at 114 VGPRs
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_mlp_infer(const float* p, const float* scaler, const float* X, float* Y, int64_t n) {
   __shared__ __bf16 w2[kH][kH + 8];
@@ -564,7 +577,7 @@ void k_mlp_infer(const float* p, const float* scaler, const float* X, float* Y, 
     for (int tc = 0; tc < 4; ++tc) {
       const f32x4 z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[tc], x, b1[tc], 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) h[tc >> 1][4 * (tc & 1) + r] = (__bf16)silu_fast(z[r]);
+      for (int r = 0; r < 4; ++r) h[tc >> 1][4 * (tc & 1) + r] = (__bf16)silu(z[r]);
     }
     bf16x8 h2[2];
 #pragma unroll
@@ -573,7 +586,7 @@ void k_mlp_infer(const float* p, const float* scaler, const float* X, float* Y, 
       z = mfma(a2[tc][0], h[0], z);
       z = mfma(a2[tc][1], h[1], z);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) h2[tc >> 1][4 * (tc & 1) + r] = (__bf16)silu_fast(z[r] + b2[tc][r]);
+      for (int r = 0; r < 4; ++r) h2[tc >> 1][4 * (tc & 1) + r] = (__bf16)silu(z[r] + b2[tc][r]);
     }
     f32x4 y = {0.f, 0.f, 0.f, 0.f};
     y = mfma(w3[0], h2[0], y);

@@ -54,3 +54,40 @@ def test_gradient_beyond_the_normal_sigmoids():
     assert float(loss.cpu()[0]) == pytest.approx(lo, rel=2e-3)
     for a, b in BLOCKS:
         assert np.linalg.norm(g[a:b] - go[a:b]) <= 2e-3 * np.linalg.norm(go[a:b]), (a, b)
+
+
+def test_inference_beyond_the_normal_sigmoids():
+    """As the gradient; standardized outputs within 2e-2 as in test_gpu_mlp.py."""
+    import torch
+    net, theta, X, _, _, _, sc = _extreme_net(17)
+    want = mlp.infer(theta, X, sc, bf16=True)
+    out = net.infer(torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
+    plain = theta.copy()
+    plain[320:4416].reshape(64, 64)[:, :8] = 0.0
+    assert np.max(np.abs(mlp.infer(plain, X, sc, bf16=True) - want) / sc["y_sd"]) > 2 * 2e-2  # the oracle's own
+    assert np.max(np.abs(out - want) / sc["y_sd"]) <= 2e-2
+
+
+@pytest.mark.parametrize("centre,third,back", [(0.0, 2.0**-16, 2.0**-40), (-20.0, 0.0, 2.0**-10), (-55.0, 0.0, 1.0)])
+def test_inference_activation_within_its_fp32_rounding(centre, third, back):
+    """One hidden unit whose pre-activation is an exact FP32 sum, brought into the range where the next
+    activation is half its argument: the output shows the BF16 activation itself.  Its FP32 value is
+    within 2.2e-7 of the true one (an ulp each of the exponential and of the sum, half an ulp each of the
+    reciprocal and of the product, at most 2^-24 of 3.7), so it may only be rounded the other way
+    within that distance of the middle between two BF16 numbers."""
+    import torch
+    import paper_1307_3711_amd as lc
+    p = mlp.unpack(np.zeros(mlp.N_PARAMS))
+    p["W1"][0, :3] = 1.0, 2.0**-8, third
+    p["b1"][0] = centre
+    p["W2"][0, 0] = back
+    p["W3"][0, 0] = 1.0
+    net = lc.Surrogate(mlp.pack(p).astype(np.float32))
+    rng = np.random.Generator(np.random.Philox(key=[5, 5]))
+    X = (rng.integers(-127, 128, (400000, 4)) / 16.0).astype(np.float32)
+    got = net.infer(torch.from_numpy(X).cuda()).cpu().numpy()[:, 0].astype(np.float64) * (2.0 / back)
+    z = X.astype(np.float64) @ p["W1"][0] + centre
+    assert np.array_equal(z, z.astype(np.float32))
+    h = mlp.silu(z)
+    lo, hi = mlp.to_bf16((h * (1.0 - 2.2e-7)).astype(np.float32)), mlp.to_bf16((h * (1.0 + 2.2e-7)).astype(np.float32))
+    assert np.all((got == lo) | (got == hi))
