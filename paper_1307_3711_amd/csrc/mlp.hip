@@ -103,7 +103,7 @@ struct TrainLds {
   float b3[kOut];
   alignas(16) float xs[kIn][kMaxBatch];  // standardized, BF16-rounded inputs
   float dy[kOut][kMaxBatch];
-  float4 corr[64];           // 1 - beta1^t, 1 - beta2^t and their reciprocals, of 64 steps
+  float3 corr[64];           // 1 - beta1^t, 1 - beta2^t and the reciprocal of the latter, of 64 steps
   float loss[kTrainWaves];
   alignas(16) float f[kH][kFPad];  // [unit][row]: hidden-2 gradient, then hidden-1 gradient
   union {                          // [unit][row]
@@ -157,18 +157,21 @@ __device__ inline float sigmoid_train(float z) {
   return 0.25f * __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), d, 1.0f);
 }
 
-// a / b with r the correctly rounded 1 / b: correctly rounded.
+// a / b with r the correctly rounded 1 / b: correctly rounded unless a is below 2^-102, where the
+// remainder is lost among the subnormal numbers.
 __device__ inline float div_by(float a, float b, float r) {
   const float q = a * r;
   return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-b, q, a), r, q), b, a);
 }
 
-// Adam (Kingma & Ba) on one FP32 master weight; c1, c2 are 1 - beta^t, r1, r2 their reciprocals.
-__device__ inline void adam(float g, float lr, float beta1, float beta2, float eps, const float4 c, float& p, float& m,
+// Adam (Kingma & Ba) on one FP32 master weight; c holds 1 - beta1^t, 1 - beta2^t and the reciprocal of
+// the latter.  The first moment has the general division (a weight of zero takes the whole quotient,
+// however small; the square root of a second moment below 2^-102 vanishes beside eps).
+__device__ inline void adam(float g, float lr, float beta1, float beta2, float eps, const float3 c, float& p, float& m,
                             float& v) {
   m = beta1 * m + (1.0f - beta1) * g;
   v = beta2 * v + (1.0f - beta2) * g * g;
-  p -= lr * div_by(m, c.x, c.z) / (sqrtf(div_by(v, c.y, c.w)) + eps);
+  p -= lr * (m / c.x) / (sqrtf(div_by(v, c.y, c.z)) + eps);
 }
 
 // Sums over the B rows (a multiple of 32) in row order, of f[r] or of f[r] g[r]: the rows of a
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
     if ((step & 63) == 0 && tid < 64) {
       const float t = (float)(t0 + step + 1 + tid);
       const float c1 = 1.0f - powf(beta1, t), c2 = 1.0f - powf(beta2, t);
-      w.corr[tid] = make_float4(c1, c2, 1.0f / c1, 1.0f / c2);
+      w.corr[tid] = make_float3(c1, c2, 1.0f / c2);
     }
     __syncthreads();
 
@@ -427,7 +430,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpState s, const f
       for (int q = 0; q < 4; ++q) grad_out[oW2 + (n0 + q) * kH + k0] = gw[q];
       if (small >= 0) grad_out[small] = gs;
     } else {
-      const float4 c = w.corr[step & 63];
+      const float3 c = w.corr[step & 63];
 #pragma unroll
       for (int q = 0; q < 4; ++q) adam(gw[q], lr, beta1, beta2, eps, c, p2[q], m2[q], v2[q]);
       if (small >= 0) adam(gs, lr, beta1, beta2, eps, c, p1, m1, v1);

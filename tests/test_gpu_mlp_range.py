@@ -91,3 +91,31 @@ def test_inference_activation_within_its_fp32_rounding(centre, third, back):
     h = mlp.silu(z)
     lo, hi = mlp.to_bf16((h * (1.0 - 2.2e-7)).astype(np.float32)), mlp.to_bf16((h * (1.0 + 2.2e-7)).astype(np.float32))
     assert np.all((got == lo) | (got == hi))
+
+
+def test_first_adam_step_bitwise_with_tiny_gradients():
+    """Weights of zero whose gradients are 1e-39 to 1e-34: Adam's first step in FP32, operation by
+    operation, bit for bit."""
+    import torch
+    import paper_1307_3711_amd as lc
+    f = np.float32
+    X, Y = toy_dataset(300, 4)
+    p = mlp.unpack(init_params(4).astype(np.float64))
+    p["W1"][:16] *= 0.02
+    p["b1"][:16] = np.linspace(-85.0, -76.0, 16)
+    p["W2"][:, :16] = 0.0
+    theta = mlp.pack(p).astype(f)
+    net = lc.Surrogate(theta)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    net.fit_scaler(Xd, Yd)
+    rows = torch.from_numpy(row_order(300, 64, 1, 5)).cuda()
+    g = net.grad(Xd, Yd, rows, 64)[0].cpu().numpy()
+    net.train(Xd, Yd, rows, 64, 1, 1e-3)
+    c1, c2 = f(1) - f(0.9), f(1) - f(0.999)
+    m, v = c1 * g, c2 * g * g
+    want = theta - f(1e-3) * (m / c1) / (np.sqrt(v / c2) + f(1e-8))
+    tiny = np.zeros(mlp.N_PARAMS, bool)
+    tiny[320:4416].reshape(64, 64)[:, :16] = True
+    small = np.abs(g[tiny])
+    assert np.sum((small > 0) & (small < 1e-37)) > 100
+    assert np.array_equal(net.params()[0], want)
