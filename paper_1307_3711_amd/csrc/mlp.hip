@@ -94,26 +94,27 @@ constexpr int kWPad = kH + 8;           // likewise for rows of units
 constexpr int kFPad = kMaxBatch + 4;    // likewise for FP32 entries
 
 struct TrainLds {
-  __bf16 w2[kH][kWPad];      // W2[n][k]
-  __bf16 w2t[kH][kWPad];     // W2[n][k] at [k][n]
+  alignas(16) __bf16 w2[kH][kWPad];   // W2[n][k]
+  alignas(16) __bf16 w2t[kH][kWPad];  // W2[n][k] at [k][n]
   float w1[kH][kIn];         // BF16-rounded
   float w3[kOut][kH];        // BF16-rounded
   alignas(16) float b1[kH];
   float b2[kH];
   float b3[kOut];
   alignas(16) float xs[kIn][kMaxBatch];  // standardized, BF16-rounded inputs
-  float dy[kOut][kMaxBatch];
+  alignas(16) float dy[kOut][kMaxBatch];
   float3 corr[64];           // 1 - beta1^t, 1 - beta2^t and the reciprocal of the latter, of 64 steps
   float loss[kTrainWaves];
   alignas(16) float f[kH][kFPad];  // [unit][row]: hidden-2 gradient, then hidden-1 gradient
   union {                          // [unit][row]
-    __bf16 h2t[kH][kColPad];       // hidden-2 activations, until their sums are taken
+    alignas(16) __bf16 h2t[kH][kColPad];  // hidden-2 activations, until their sums are taken
     struct {                       // the operands of dW2
-      __bf16 h1t[kH][kColPad];
-      __bf16 d2t[kH][kColPad];
+      alignas(16) __bf16 h1t[kH][kColPad];
+      alignas(16) __bf16 d2t[kH][kColPad];
     };
   };
 };
+static_assert(kWPad % 8 == 0 && kColPad % 8 == 0 && kFPad % 4 == 0, "16-byte reads of every row");
 static_assert(sizeof(TrainLds) <= 160 * 1024, "LDS of one compute unit");
 
 // Master parameter outside W2 that a thread updates (-1: none): waves 0 and 1 the rows of W3,
@@ -540,7 +541,7 @@ __device__ inline float silu(float z) {
 constexpr int kInferBlocks = 256 * 4;  // four blocks of four waves fit on each compute unit at 114 VGPRs
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 void k_mlp_infer(const float* p, const float* scaler, const float* X, float* Y, int64_t n) {
-  __shared__ __bf16 w2[kH][kH + 8];
+  __shared__ alignas(16) __bf16 w2[kH][kWPad];
   for (int i = threadIdx.x; i < kH * kH; i += 256) w2[i / kH][i % kH] = (__bf16)p[oW2 + i];
   const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
