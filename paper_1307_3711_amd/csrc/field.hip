@@ -252,7 +252,7 @@ void k_field_pairs(const double* __restrict__ xyzq, int64_t n, double eps2d, T* 
     sb[3 * kN3Slice + lane] = sb[3 * kN3Slice + lane + 64] = q;
     wave_lds_sync();
 #define LC_CHUNK(US, UT, JS)                                                                                      \
-  n3_chunk<T, R, US, UT, JS, false, PHI>(sb, lane, xi, yi, zi, qi, eps2, f[0], f[1], f[2], a[0], a[1], a[2], T(0), T(0), \
+  n3_chunk<T, R, 2, US, UT, JS, false, PHI>(sb, lane, xi, yi, zi, qi, eps2, f[0], f[1], f[2], a[0], a[1], a[2], T(0), T(0), \
                                          f[3], &a[3], w)
     if (jside) {
       if (us) {

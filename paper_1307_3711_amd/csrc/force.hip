@@ -566,6 +566,10 @@ __device__ void tile_n3(const N3Args<T>& a, int t, T* lds) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = w / WJ, jw = w % WJ;
   const bool jside = (I != J);
+  // Rotations per register buffer: two from R = 2 on, where four spill at five waves per SIMD.  R = 2,
+  // WJ = 1 has four waves (see k_force_n3) and keeps four: its one or two waves per SIMD below 20,000
+  // macroparticles wait for LDS (a step of 6000: 47.8 us, with two 50.4; of 20,000 128.5 and 124.2).
+  constexpr int kRotations = sizeof(T) == 4 && (R == 1 || (R == 2 && WJ == 1)) ? 4 : 2;
   // rows exist only for blocks holding live slots (I <= J < nb <= M for a table built for n)
   const bool live = (int64_t)J * B < n && I <= J && J < a.M;
   T* sb = lds + w * 4 * kN3Slice;  // x, y, z, q arrays of the wave's chunk
@@ -644,18 +648,21 @@ __device__ void tile_n3(const N3Args<T>& a, int t, T* lds) {
       T cx[R], cy[R], cz[R], ax, ay, az;
 #pragma unroll
       for (int r = 0; r < R; ++r) cx[r] = cy[r] = cz[r] = 0;
+#define LC_CHUNK(US, UT, JS) \
+  n3_chunk<T, R, kRotations, US, UT, JS, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL)
       if (jside) {
         if (us) {
-          if (ut) n3_chunk<T, R, true, true, true, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
-          else n3_chunk<T, R, true, false, true, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
+          if (ut) LC_CHUNK(true, true, true);
+          else LC_CHUNK(true, false, true);
         } else {
-          if (ut) n3_chunk<T, R, false, true, true, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
-          else n3_chunk<T, R, false, false, true, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
+          if (ut) LC_CHUNK(false, true, true);
+          else LC_CHUNK(false, false, true);
         }
       } else {
-        if (us) n3_chunk<T, R, true, true, false, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
-        else n3_chunk<T, R, false, true, false, PBC>(sb, lane, xi, yi, zi, qi, eps2f, cx, cy, cz, ax, ay, az, L, iL);
+        if (us) LC_CHUNK(true, true, false);
+        else LC_CHUNK(false, true, false);
       }
+#undef LC_CHUNK
       wave_lds_sync();
       const T fs = us ? qs0 : T(1);
 #pragma unroll
@@ -770,11 +777,11 @@ __global__ __launch_bounds__(64 * kFoldWaves) void k_fold_n3(DevState s, RunCons
 // ----------------------------------------------------------------------------- kernels
 // Occupancy the register allocation aims at: 5 waves per SIMD for FP32 pairs (96 VGPRs at R = WJ =
 // 4, three values of some pair loops spilled; 20,000 macroparticles 87.1 us, with 4 waves and no spills
-// 90.9; 4 from R = 6 and at R = 4, WJ = 2: 110.8 against 112.1 us), 3 for FP64 pairs (twice the
-// registers per value; 2 from R = 5).
+// 90.9; 4 from R = 6, at R = 4, WJ = 2 (110.8 against 112.1 us) and at R = 2, WJ = 1), 3 for FP64 pairs
+// (twice the registers per value; 2 from R = 5).
 template <typename T, int R, int WJ, bool PBC>
 __global__ __launch_bounds__(64 * n3_waves(R, WJ))
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (R >= 5 ? 2 : 3) : (R >= 6 || (R == 4 && WJ == 2) ? 4 : 5))))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (R >= 5 ? 2 : 3) : (R >= 6 || (R == 4 && WJ == 2) || (R == 2 && WJ == 1) ? 4 : 5))))
 void k_force_n3(N3Args<T> a) {
   extern __shared__ __align__(16) unsigned char lds_n3_raw[];
   T* lds_n3 = reinterpret_cast<T*>(lds_n3_raw);

@@ -130,7 +130,7 @@ template <typename T, int R, int U, bool US, bool UT, bool JSIDE, bool PBC, bool
 __device__ inline void n3_steps(const T* bx, const T* by, const T* bz, const T* bq, const T* xi, const T* yi,
                                 const T* zi, const T* qi, T eps2f, T* fx, T* fy, T* fz, T& rx, T& ry, T& rz, T L,
                                 T iL, T* fp = nullptr, T* rp = nullptr, int self = -1) {
-  constexpr int G = sizeof(T) == 4 && R * U <= 8 ? U : 1;  // rotations and targets of a group
+  constexpr int G = sizeof(T) == 8 || R > 4 ? 1 : R == 1 ? U : 2;  // rotations and targets of a group
   constexpr int GR = sizeof(T) == 4 ? R : 1;
 #pragma unroll
   for (int u0 = 0; u0 < U; u0 += G) {
@@ -209,14 +209,13 @@ __device__ inline void n3_load(const T* sx, int k, T* bx, T* by, T* bz, T* bq) {
 // the lane's R targets.  US: all sources of the chunk carry one charge (factored out by the
 // caller); UT: likewise for the targets of the wave.  JSIDE: also the reaction sums
 // sum_r q_r s_r (r_i - r_j) of the chunk's sources, returned in (ax, ay, az) of lane l for
-// source l.  Software pipelined over two register buffers: the sources of the next U
+// source l.  Software pipelined over two register buffers of U rotations: the sources of the next U
 // rotations are read while the current U are used (the slice has kN3Slice >= 128 + U
 // entries, so the read after the last rotation stays inside it).
-template <typename T, int R, bool US, bool UT, bool JSIDE, bool PBC, bool PHI = false>
+template <typename T, int R, int U, bool US, bool UT, bool JSIDE, bool PBC, bool PHI = false>
 __device__ inline void n3_chunk(const T* sb, int lane, const T* xi, const T* yi, const T* zi, const T* qi, T eps2f,
                                 T* fx, T* fy, T* fz, T& ax, T& ay, T& az, T L, T iL, T* fp = nullptr,
                                 T* ap = nullptr, int self = -1) {
-  constexpr int U = (R >= 2 || sizeof(T) == 8) ? 2 : 4;  // rotations per register buffer
   static_assert(128 + U <= kN3Slice && 64 % (2 * U) == 0, "prefetch stays inside the wave's slice");
   const T* sx = sb + lane;
   T rx = 0, ry = 0, rz = 0, rp = 0;  // running sums of source (lane + k) mod 64
