@@ -1589,7 +1589,7 @@ bool field_in_place(int64_t n, const double* d_xyzq, const double* d_E, const do
 hipError_t launch_field(int precision, int64_t n, const double* xyzq, double eps2, double* E, double* phi, void* work,
                         size_t work_bytes, const lc_tuning* t, const ForceTiling& ft, hipStream_t st) {
   if (tuning_default(t) && !field_in_place(n, xyzq, E, phi))
-    return launch_field_default(precision, n, xyzq, eps2, E, phi, work, work_bytes, st);
+    return launch_field_default(precision, n, xyzq, eps2, E, phi, work, work_bytes, ft, st);
   return launch_field_standalone(precision, n, xyzq, eps2, E, phi, work, ft, st);
 }
 

@@ -360,7 +360,7 @@ __global__ __launch_bounds__(64 * kFoldWaves) void k_field_fold(const T* __restr
   }
 }
 
-// Rows a strip may hold, and the end of the strip that starts at J0 (J1^2 - J0^2 rows).
+// Rows a strip may hold (the strip of blocks J0 .. J1 - 1 has J1^2 - J0^2).
 template <typename T, bool PHI>
 int64_t strip_rows() {
   return (int64_t)(LC_FIELD_STATIC_MAX_BYTES / (sizeof(T) * (PHI ? 4 : 3) * kPB));
@@ -388,16 +388,33 @@ hipError_t launch_pairs(int64_t n, const double* xyzq, double eps2, double* E, d
 
 using namespace field_default;
 
-// Each pair once past 4096 charges, as long as a strip can hold the rows of one J (up to about a
-// million charges).  Up to there the direct kernel has one block of 16 targets per compute unit at
+// Each pair once past 4096 charges, as long as a strip can hold the rows of one J (up to 1,048,576
+// charges in FP64 and 2,097,152 in FP32).  Up to there the direct kernel has one block of 16 targets per compute unit at
 // most (4096 charges with the potential: 13.1 us in FP32 and 18.6 us in FP64, each pair once 18.6 and
 // 22.2 us), beyond some have two (4099: 20.1 and 30.7 us against 18.8 and 22.2 us).  Kahan sums have
 // no form that takes each pair once.
 constexpr int64_t kPairsFrom = 16 * kUnits + 1;
-bool field_pairs(int precision, int64_t n) {
-  if (precision == LC_FP32_KAHAN || n < kPairsFrom) return false;
+bool strip_holds(int precision, int64_t n) {
   const int64_t nb = (n + kPB - 1) / kPB;
   return 2 * nb - 1 <= (precision == LC_FP64 ? strip_rows<double, true>() : strip_rows<float, true>());
+}
+bool field_pairs(int precision, int64_t n) {
+  return precision != LC_FP32_KAHAN && n >= kPairsFrom && strip_holds(precision, n);
+}
+
+// Whether the one-sided kernel of force.hip takes a call that cannot take each pair once, for want of
+// workspace or of rows in a strip.  Its blocks of 256 R targets (R = 4 in FP32, 2 in FP64) come in
+// rounds of one per compute unit; with two rounds in FP32 and four in FP64 it is ahead of the direct kernel
+// where the last round is nearly full: ms without the potential, one-sided and direct, FP32 520,000
+// charges 92.8 and 95.8, 530,000 139 and 100, 780,000 203 and 217, 800,000 270 and 227; FP64 450,000
+// 145 and 141, 520,000 170 and 187, 530,000 211 and 196, 600,000 240 and 251.  Beyond the strips it
+// takes every call: FP32 2,100,000 1518 and 1561, FP64 1,060,000 743 and 776, 1,450,000 1340 and 1449.
+bool field_one_sided(int precision, int64_t n) {
+  if (precision == LC_FP32_KAHAN) return false;
+  if (!strip_holds(precision, n)) return true;
+  const bool wide = precision == LC_FP64;
+  const int64_t round = kUnits * 256 * (wide ? 2 : 4), rounds = (n + round - 1) / round;
+  return rounds >= (wide ? 4 : 2) && 100 * rounds * round <= (wide ? 110 : 105) * n;
 }
 
 size_t field_default_bytes(int precision, int64_t n) {
@@ -408,7 +425,7 @@ size_t field_default_bytes(int precision, int64_t n) {
 }
 
 hipError_t launch_field_default(int precision, int64_t n, const double* xyzq, double eps2, double* E, double* phi,
-                                void* work, size_t work_bytes, hipStream_t st) {
+                                void* work, size_t work_bytes, const ForceTiling& ft, hipStream_t st) {
   if (n == 0) return hipSuccess;
   if (field_pairs(precision, n) && work_bytes >= field_default_bytes(precision, n)) {
     if (precision == LC_FP64)
@@ -417,6 +434,7 @@ hipError_t launch_field_default(int precision, int64_t n, const double* xyzq, do
     return phi ? launch_pairs<float, true>(n, xyzq, eps2, E, phi, work, st)
                : launch_pairs<float, false>(n, xyzq, eps2, E, phi, work, st);
   }
+  if (field_one_sided(precision, n)) return launch_field_standalone(precision, n, xyzq, eps2, E, phi, work, ft, st);
   if (precision == LC_FP64) return launch_direct<double, 16, 16, false>(n, xyzq, eps2, E, phi, st);
   if (precision != LC_FP32_KAHAN) return launch_direct<float, 16, 16, false>(n, xyzq, eps2, E, phi, st);
   // Kahan sums of any size: up to a block of 16 targets per compute unit 16 waves each, beyond 8 waves

@@ -443,11 +443,11 @@ hipError_t launch_refresh_sources(const DevState& s, const RunConst& rc, int pre
 // Standalone field (lc_field).
 hipError_t launch_field_standalone(int precision, int64_t n, const double* xyzq, double eps2, double* E,
                                    double* phi, void* work, const ForceTiling& ft, hipStream_t st);
-// The same with the default tiling (field.hip): field_default_bytes of workspace where each pair is
-// taken once (0: none is used); with less the one-sided kernel runs.
+// The same for a default call (field.hip): field_default_bytes of workspace where each pair is taken
+// once (0: it is not); with less the direct kernel runs, or launch_field_standalone with tiling ft.
 size_t field_default_bytes(int precision, int64_t n);
 hipError_t launch_field_default(int precision, int64_t n, const double* xyzq, double eps2, double* E, double* phi,
-                                void* work, size_t work_bytes, hipStream_t st);
+                                void* work, size_t work_bytes, const ForceTiling& ft, hipStream_t st);
 size_t field_workspace_bytes(int precision, int64_t n, const ForceTiling& ft);
 // Device address of the current device's lc_field_static workspace (LC_FIELD_STATIC_MAX_BYTES),
 // looked up on the first call per device.
