@@ -57,13 +57,13 @@ __device__ inline void direct_pair(const V4 s, bool live, bool self, T eps2, Lan
   r2 = n3_fma(dy, dy, r2);
   r2 = n3_fma(dz, dz, r2);
   T qinv = 0, sc;
-  if (PHI || sizeof(T) == 4) {
+  if constexpr (PHI || sizeof(T) == 4) {
     T inv = n3_rsq(r2);
     if (MASK && !live) inv = 0;
     qinv = UNIFORM ? inv : s.w * inv;
     sc = qinv * (inv * inv);
   } else {
-    sc = n3_cubed(r2);
+    sc = rsq64_cubed<false>(r2);
     if (MASK && !live) sc = 0;
     if (!UNIFORM) sc *= s.w;
   }

@@ -57,13 +57,6 @@ template <> struct N3Type<double> {
   static constexpr double kFar = 1e150;
 };
 
-// x^{-3/2}; the FP32 form shares its reciprocal root with the potential, the FP64 one does not.
-__device__ inline float n3_cubed(float x) {
-  const float inv = rsq32(x);
-  return inv * (inv * inv);
-}
-__device__ inline double n3_cubed(double x) { return rsq64_cubed<false>(x); }
-
 __device__ inline float n3_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ inline double n3_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
