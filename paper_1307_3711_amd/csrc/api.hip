@@ -533,10 +533,16 @@ int latched_error(lc_sim* s) {
   return error_of_flags(s, err);
 }
 
+// A handle may be destroyed while the thread captures another stream: the buffer then goes back in
+// relaxed capture mode, where the runtime does not refuse it.
 void free_read_buffer(lc_sim* s) {
+  if (!s->rb.head) return;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
   for (auto& ev : s->rb.done)
     if (ev) (void)hipEventDestroy(ev);
-  if (s->rb.head) (void)hipHostFree(s->rb.head);
+  (void)hipHostFree(s->rb.head);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
   s->rb = ReadBuffer{};
 }
 

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../include/lcmd.h"
@@ -22,7 +23,9 @@ struct Event { int device; };
 int g_current = 0;      // current device
 int g_state_device = 1; // device of every address asked for
 int64_t g_live = 0;     // what the packing kernel reports
-int g_packs = 0, g_packs_elsewhere = 0, g_host_mallocs = 0, g_bad_records = 0;
+int g_packs = 0, g_packs_elsewhere = 0, g_host_mallocs = 0, g_host_frees = 0, g_bad_records = 0;
+bool g_global_capture = false;  // the thread captures some other stream, in the strictest mode
+hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal;
 std::map<const void*, std::string> g_kernels;
 dim3 g_grid, g_block;
 size_t g_lds;
@@ -51,7 +54,13 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
-hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostFree(void* p) {
+  if (g_global_capture && g_mode != hipStreamCaptureModeRelaxed) return hipErrorStreamCaptureUnsupported;
+  ++g_host_frees;
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode) { std::swap(*mode, g_mode); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { return capturing(s) ? hipErrorStreamCaptureUnsupported : hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
   *st = capturing(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -187,7 +196,12 @@ int main() {
   dev1.capturing = false;
   check(lc_read_particles(sim, 0, x.data(), nullptr, nullptr, nullptr, nullptr, n, &got) == LC_OK && got == n,
         "particles read after the capture");
+  // destroyed while another stream is captured: the pinned buffer is given back all the same
+  g_global_capture = true;
+  const int frees = g_host_frees;
   lc_destroy(sim);
+  check(g_host_frees == frees + 1, "the pinned buffer freed during another stream's capture");
+  check(g_mode == hipStreamCaptureModeGlobal, "the thread's capture mode as before");
   std::printf("bad %d\n", bad);
   return bad;
 }
