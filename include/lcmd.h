@@ -20,7 +20,8 @@
  *     the caller queries lc_state_bytes(), allocates that many bytes (any allocator; 256-B
  *     alignment) and passes the pointer to lc_create(); lc_field() takes a caller-owned
  *     workspace sized by lc_field_workspace_bytes().  Host pointers stay owned by the
- *     caller and are only read or written during the call.
+ *     caller and are only read or written during the call.  A handle holds 0.5 MB of pinned
+ *     host memory from its first lc_read_particles or lc_read_diagnostics to lc_destroy.
  *   - Work is enqueued asynchronously on the HIP stream given at creation (a hipStream_t
  *     passed as void*; NULL is the null stream).  Only lc_read_* and lc_autotune
  *     synchronize that stream.
@@ -356,9 +357,12 @@ size_t lc_field_workspace_bytes(int32_t precision, int64_t n, const lc_tuning* t
  *   phi_i = sum_{j != i} q_j / (|r_i - r_j|^2 + eps^2)^{1/2}        (if d_phi != NULL)
  * d_xyzq: device, 4 n doubles laid out x[n], y[n], z[n], q[n] (q in field units).
  * d_E: device, 3 n doubles out, laid out Ex[n], Ey[n], Ez[n].  d_work: caller-owned device
- * workspace of at least lc_field_workspace_bytes().  Asynchronous on hip_stream.  d_E and d_phi
- * may lie over d_xyzq (not over each other or d_work): a default call (t = NULL or all zeros)
- * then runs the one-sided kernel, with its results.
+ * workspace of at least lc_field_workspace_bytes(); a default call (t = NULL or all zeros) also
+ * takes the bytes of one split, lc_field_workspace_bytes() of a tiling with j_splits = 1 alone, and
+ * then, where it asks for more, another kernel whose sums are rounded in another order.
+ * Asynchronous on hip_stream.  d_E and d_phi
+ * may lie over d_xyzq (not over each other or d_work): a default call then runs the one-sided
+ * kernel, with its results.
  * A tiling with newton3 = 1 computes E only (d_phi must be NULL).
  * LC_E_INVALID for n < 0, n > 2^30, eps2 <= 0, a workspace that is too small or not 256-byte
  * aligned, or an unknown tiling; LC_E_HIP when a launch fails (also for a request of more than
@@ -368,8 +372,8 @@ int lc_field(int32_t precision, int64_t n, const double* d_xyzq, double eps2, do
 
 /* Allocation-free variant of lc_field for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * kernels and results as lc_field (bitwise, for the same arguments and tiling), with the
- * workspace in a device array of LC_FIELD_STATIC_MAX_BYTES that the library holds on every
+ * kernels and results as lc_field with a workspace of lc_field_workspace_bytes() (bitwise, for
+ * the same arguments and tiling), with the workspace in a device array of LC_FIELD_STATIC_MAX_BYTES that the library holds on every
  * device it runs on until the process ends, instead of a caller-owned d_work.  The caller still
  * passes the inputs and outputs.  Calls nothing that allocates; the first call on a device
  * looks the array's address up (make it outside graph capture).  LC_E_INVALID as lc_field,

@@ -383,8 +383,10 @@ int choose_splits(const lc_sim* s, const ForceTiling& ft) {
   return S;
 }
 
-// The one-sided tiling of a handle whose caller asked for none, from the particle counts (with
-// ionization the capacities, so that a run saved and loaded keeps its tiling).
+// The one-sided tiling of a handle whose caller asked for none, from the particle counts, with
+// ionization the capacities, so that a run saved and loaded keeps its tiling.  Only the splits of FP32
+// runs come from the host's counts (choose_splits, as with default_tiling); a checkpoint holds the
+// splits in use.
 // FP32: default_tiling's splits and segments with one target per lane instead of four: four times
 // the blocks, and every target's sum in the same order, so the same bits.  A pass over 3000
 // macroparticles: 27.7 -> 10.0 us.  Sources come from LDS, below 2048 macroparticles through the

@@ -781,7 +781,8 @@ __global__ __launch_bounds__(64 * kFoldWaves) void k_fold_n3(DevState s, RunCons
 // (twice the registers per value; 2 from R = 5).
 template <typename T, int R, int WJ, bool PBC>
 __global__ __launch_bounds__(64 * n3_waves(R, WJ))
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (R >= 5 ? 2 : 3) : (R >= 6 || (R == 4 && WJ == 2) || (R == 2 && WJ == 1) ? 4 : 5))))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? (R >= 5 ? 2 : 3)
+                                                  : (R >= 6 || (R == 4 && WJ == 2) || (R == 2 && WJ == 1) ? 4 : 5))))
 void k_force_n3(N3Args<T> a) {
   extern __shared__ __align__(16) unsigned char lds_n3_raw[];
   T* lds_n3 = reinterpret_cast<T*>(lds_n3_raw);

@@ -81,12 +81,13 @@ __device__ inline int weight_row(int tc, int m) { return unit_of(4 * tc + (m & 3
 // parameters it updates, with their Adam moments, in registers over all steps.  What crosses
 // waves goes through LDS, four barriers a step.
 // Bound by the VALU issue of one compute unit (the two SiLUs and their derivatives of 256 rows are
-// most of it: 10.8 us; the sums over rows 3.9, Adam 1.2).  Measured at 256 rows: 17.1 us a step,
-// against 200 us with four waves that kept every activation in global memory; with the sums over
-// rows on one LDS read per row 24.2 us, and with expf's range checks, the general division and the
-// first layer on the VALU 29 us.  Every sum keeps its order and every operation its rounding, so
-// trained weights are the same bits in all of these.  The transposing LDS read in place of the
-// transposed arrays' 2-byte writes was no faster (18.3 and 19.1 us).
+// most of it: 10.8 us; the sums over rows 3.9, Adam 1.2).  Measured at 256 rows: 17.4 us a step (17.1
+// without the subnormal sigmoids and the general division of the first moment), against 200 us with
+// four waves that kept every activation in global memory; with the sums over rows on one LDS read per
+// row 24.2 us, and with expf's range checks, the general division everywhere and the first layer on
+// the VALU 29 us.  Every sum keeps its order and every operation its rounding, so trained weights are
+// the same bits in all of these.  The transposing LDS read in place of the transposed arrays' 2-byte
+// writes was no faster (18.3 and 19.1 us).
 constexpr int kTrainWaves = 16;
 constexpr int kTrainThreads = 64 * kTrainWaves;
 constexpr int kColPad = kMaxBatch + 8;  // entries of a transposed row: 16-byte reads of 16 rows meet no bank twice
@@ -533,8 +534,8 @@ __device__ inline float silu(float z) {
 
 // A wave walks over tiles of 16 rows with every weight in registers: layer 1 on the FP32 matrix
 // units (K = 4 is the input width: lane l brings input l / 16 of row l % 16, one coalesced load),
-// layers 2 and 3 on the BF16 ones, the SiLU on the VALU, which bounds it (32 of them are 480 of about
-// 560 issue slots a tile: 57 us for a million rows; the 24 MB they move take 5 us).  No LDS and no
+// layers 2 and 3 on the BF16 ones, the SiLU on the VALU, which bounds it (32 of them are 480 of 575
+// issue slots a tile: 58 us for a million rows; the 24 MB they move take 5 us).  No LDS and no
 // barrier in the loop.  Measured on a million rows, back to back: 70.8 us, against 398 us with the weights
 // staged and converted for every 64 rows, the inputs standardized once per unit and the outer layers on
 // the VALU, 83.5 us with the SiLU of the training kernel, and 47 us with the less exact one.
